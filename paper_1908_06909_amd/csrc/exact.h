@@ -15,6 +15,16 @@
 // expanded by multilinearity into at most 48 such triple products and summed
 // exactly.  The sign of a non-overlapping expansion is the sign of its
 // largest component.
+//
+// Nearly all determinants that get here have columns whose entries, scaled by
+// a power of two of the column's own, are integers below 2^41 (mesh and
+// detector coordinates of similar size).  Those are decided in 128-bit integer
+// arithmetic: some 500 instructions in registers, against several thousand
+// dependent ones on an array in scratch memory for the expansion, which one
+// ray through an edge makes its whole wavefront wait for, several times in a
+// row: a walk of 65,536 rays through 3,072 tetrahedra, 1,077 signs of it
+// ties, takes 0.10 ms with the integers and 0.37 with the expansion; one of
+// 2.9M rays with 3.1M ties 5.1 ms and 8.1.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -77,8 +87,9 @@ __host__ __device__ inline int expansion_add_det(double* e, int n, const float* 
 // det[X, Y, Z] over X in {A1, A0}, Y in {B1, B0}, Z in {C1, C0}, the sign
 // being (-1)^(number of *0 picks); picks of a null pointer or of the same
 // point twice contribute exactly zero and are skipped.
-__host__ __device__ inline int exact_det_diff_sign(const float* A1, const float* A0, const float* B1,
-                                                   const float* B0, const float* C1, const float* C0) {
+__host__ __device__ __attribute__((noinline)) inline int expansion_det_diff_sign(const float* A1, const float* A0,
+                                                                                 const float* B1, const float* B0,
+                                                                                 const float* C1, const float* C0) {
   double e[96];
   int n = 0;
   const float* As[2] = {A1, A0};
@@ -93,6 +104,57 @@ __host__ __device__ inline int exact_det_diff_sign(const float* A1, const float*
       }
   if (n == 0) return 0;
   return e[n - 1] > 0.0 ? 1 : -1;
+}
+
+// The column a1 - a0 times a power of two as integers, |c| <= 2^41; false when
+// a scaled coordinate is not an integer below 2^51.  (The scale puts the
+// largest difference, rounded, into [2^40, 2^41); a0 = null is zero.)
+__host__ __device__ inline bool column_to_int(const float* a1, const float* a0, long long* c) {
+  double x1[3], x0[3];
+  double m = 0.0;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    x1[i] = (double)a1[i];
+    x0[i] = a0 ? (double)a0[i] : 0.0;
+    m = fmax(m, fabs(x1[i] - x0[i]));
+  }
+  int e = 0;
+  (void)frexp(m, &e);  // m = 0 (a zero column): e = 0
+  bool ok = true;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    // y = x + 1.5 2^52 rounds x to an integer, whose value is the difference
+    // of the bit patterns of y and 1.5 2^52.
+    const double p = ldexp(x1[i], 41 - e), q = ldexp(x0[i], 41 - e);
+    const double yp = p + 0x1.8p52, yq = q + 0x1.8p52;
+    ok = ok && fabs(p) < 0x1p51 && fabs(q) < 0x1p51 && yp - 0x1.8p52 == p && yq - 0x1.8p52 == q;
+    c[i] = __builtin_bit_cast(long long, yp) - __builtin_bit_cast(long long, yq);
+  }
+  return ok;
+}
+
+// Sign of det[a, b, c] for |entries| <= 2^41: the minors stay below 2^83.01 and
+// the determinant below 2^125.6.  A loop over the first column's entries,
+// rows rotated, to save registers and instructions.
+__host__ __device__ inline int int_det_sign(const long long* a, const long long* b, const long long* c) {
+  typedef __int128 i128;
+  long long a0 = a[0], a1 = a[1], a2 = a[2], b0 = b[0], b1 = b[1], b2 = b[2], c0 = c[0], c1 = c[1], c2 = c[2];
+  i128 d = 0;
+#pragma unroll 1
+  for (int i = 0; i < 3; ++i) {
+    d += (i128)a0 * ((i128)b1 * c2 - (i128)b2 * c1);
+    const long long ta = a0, tb = b0, tc = c0;
+    a0 = a1;
+    a1 = a2;
+    a2 = ta;
+    b0 = b1;
+    b1 = b2;
+    b2 = tb;
+    c0 = c1;
+    c1 = c2;
+    c2 = tc;
+  }
+  return d > 0 ? 1 : (d < 0 ? -1 : 0);
 }
 
 // Float64 estimate of the same determinant with a certified error bound.
@@ -125,12 +187,25 @@ __host__ __device__ inline int filtered_det_diff_sign(const float* A1, const flo
 
 enum SignFlags : unsigned { kFlagExact = 1u, kFlagPerturbed = 2u };
 
-__host__ __device__ inline int det_diff_sign(const float* A1, const float* A0, const float* B1, const float* B0,
-                                             const float* C1, const float* C0, unsigned* flags) {
+// The same sign from the filter or, behind it, the integers alone; 2 when
+// neither applies (a column without an integer form).
+__host__ __device__ inline int quick_det_diff_sign(const float* A1, const float* A0, const float* B1,
+                                                   const float* B0, const float* C1, const float* C0,
+                                                   unsigned* flags) {
   int s = filtered_det_diff_sign(A1, A0, B1, B0, C1, C0);
   if (s != 2) return s;
   if (flags) *flags |= kFlagExact;
-  return exact_det_diff_sign(A1, A0, B1, B0, C1, C0);
+  long long a[3], b[3], c[3];
+  const bool ka = column_to_int(A1, A0, a);
+  const bool kb = column_to_int(B1, B0, b);
+  const bool kc = column_to_int(C1, C0, c);
+  return ka && kb && kc ? int_det_sign(a, b, c) : 2;
+}
+
+__host__ __device__ inline int det_diff_sign(const float* A1, const float* A0, const float* B1, const float* B0,
+                                             const float* C1, const float* C0, unsigned* flags) {
+  const int s = quick_det_diff_sign(A1, A0, B1, B0, C1, C0, flags);
+  return s != 2 ? s : expansion_det_diff_sign(A1, A0, B1, B0, C1, C0);
 }
 
 // orient3d(a, b, c, d) = sign det[b - a, c - a, d - a].
@@ -140,15 +215,25 @@ __host__ __device__ inline int orient3d_sign(const float* a, const float* b, con
 
 // Sign of the edge (p, q) seen by the ray S -> P translated by eps U + eps^2 V:
 // det[P - S, p - S, q - S], else det[P - S, U, p - q], else det[P - S, V, p - q].
-// Zero only for an edge parallel to P - S.
+// Zero only for an edge parallel to P - S.  kQuick: 2 when a determinant needs
+// the expansion (a walk that calls this loses the registers that it uses, so
+// the quick form makes no call of its own).
+template <bool kQuick>
 __host__ __device__ inline int perturbed_edge_sign(const float* S, const float* P, const float* U, const float* V,
                                                    const float* p, const float* q, unsigned* flags) {
-  int s = det_diff_sign(P, S, p, S, q, S, flags);
-  if (s != 0) return s;
-  if (flags) *flags |= kFlagPerturbed;
-  s = det_diff_sign(P, S, U, nullptr, p, q, flags);
-  if (s != 0) return s;
-  return det_diff_sign(P, S, V, nullptr, p, q, flags);
+  const float *B1 = p, *B0 = S, *C1 = q, *C0 = S;
+  int s = 0;
+#pragma unroll
+  for (int level = 0; level < 3; ++level) {
+    s = kQuick ? quick_det_diff_sign(P, S, B1, B0, C1, C0, flags) : det_diff_sign(P, S, B1, B0, C1, C0, flags);
+    if (s != 0) break;
+    if (flags) *flags |= kFlagPerturbed;
+    B1 = level == 0 ? U : V;
+    B0 = nullptr;
+    C1 = p;
+    C0 = q;
+  }
+  return s;
 }
 
 }  // namespace tct

@@ -26,13 +26,29 @@ __device__ __forceinline__ float3 pixel_point(const float* f, float u, float v) 
 }
 
 // Exact perturbed sign of the edge (p, q): returns sign + 1 in bits 0-1 and
-// the exact.h flags in bits 2-3.
-__device__ __noinline__ int slow_edge_sign(float3 S, float3 P, float3 U, float3 V, float3 p, float3 q) {
+// the exact.h flags in bits 2-3.  Sign 2 (bits 0-1 = 3) comes only from
+// quick_edge_sign: the expansion has to decide.
+template <bool kQuick>
+__device__ __forceinline__ int edge_sign_bits(float3 S, float3 P, float3 U, float3 V, float3 p, float3 q) {
   float s[3] = {S.x, S.y, S.z}, pp[3] = {P.x, P.y, P.z}, u[3] = {U.x, U.y, U.z}, v[3] = {V.x, V.y, V.z};
   float a[3] = {p.x, p.y, p.z}, b[3] = {q.x, q.y, q.z};
   unsigned flags = 0;
-  int sg = perturbed_edge_sign(s, pp, u, v, a, b, &flags);
+  int sg = perturbed_edge_sign<kQuick>(s, pp, u, v, a, b, &flags);
   return (sg + 1) | (int)(flags << 2);
+}
+
+__device__ __noinline__ int quick_edge_sign(float3 S, float3 P, float3 U, float3 V, float3 p, float3 q) {
+  return edge_sign_bits<true>(S, P, U, V, p, q);
+}
+
+__device__ __noinline__ int expansion_edge_sign(float3 S, float3 P, float3 U, float3 V, float3 p, float3 q) {
+  return edge_sign_bits<false>(S, P, U, V, p, q);
+}
+
+__device__ __forceinline__ int slow_edge_sign(float3 S, float3 P, float3 U, float3 V, float3 p, float3 q) {
+  int r = quick_edge_sign(S, P, U, V, p, q);
+  if (__builtin_expect((r & 3) == 3, 0)) r = expansion_edge_sign(S, P, U, V, p, q);
+  return r;
 }
 
 }  // namespace

@@ -531,17 +531,28 @@ __device__ __forceinline__ bool walk_step(const MeshView& M, const Ray& r, const
   const float3 D = g.D, e0 = g.e0, e1 = g.e1, e2 = g.e2;
   // One bound from the longest edge settles all three signs in the common
   // case; otherwise each edge gets its own bound before any float64 work.
+  // (The branches that call out are marked as unlikely: the registers that a
+  // call clobbers are then saved around it, not moved out of the whole loop.)
   int k = step_exit_common(g);
-  if (k < 0) {
+  if (__builtin_expect(k < 0, 0)) {
     int s0 = step_edge_certified(g.E0, g.m0, g.K);
     int s1 = step_edge_certified(g.E1, g.m1, g.K);
     int s2 = step_edge_certified(g.E2, g.m2, g.K);
-    if (s0 == 0) s0 = resolve_src(q, v, w.a0, st);
-    if (s1 == 0) s1 = resolve_src(q, v, w.a1, st);
-    if (s2 == 0) s2 = resolve_src(q, v, w.a2, st);
+    // One place that calls out, in a loop over the edges.
+#pragma unroll 1
+    for (int i = 0; i < 3; ++i) {
+      if ((i == 0 ? s0 : i == 1 ? s1 : s2) != 0) continue;
+      const float3 a = make_float3(i == 0 ? w.a0.x : i == 1 ? w.a1.x : w.a2.x,
+                                   i == 0 ? w.a0.y : i == 1 ? w.a1.y : w.a2.y,
+                                   i == 0 ? w.a0.z : i == 1 ? w.a1.z : w.a2.z);
+      const int sg = resolve_src(q, v, a, st);
+      s0 = i == 0 ? sg : s0;
+      s1 = i == 1 ? sg : s1;
+      s2 = i == 2 ? sg : s2;
+    }
     k = exit_slot(s0, s1, s2);
   }
-  if (k == 3) {
+  if (__builtin_expect(k == 3, 0)) {
     st.add_failed();
     st.steps += w.steps;
     return false;
@@ -562,7 +573,7 @@ __device__ __forceinline__ bool walk_step(const MeshView& M, const Ray& r, const
   float3 n = f3cross(ei, ej);
   float den = f3dot(r.d, n);
   float dt;
-  if (fabsf(den) > r.gd * fmaxf(fabsf(n.x), fmaxf(fabsf(n.y), fabsf(n.z)))) {
+  if (__builtin_expect(fabsf(den) > r.gd * fmaxf(fabsf(n.x), fmaxf(fabsf(n.y), fabsf(n.z))), 1)) {
     dt = f3dot(D, n) * __builtin_amdgcn_rcpf(den);  // v_rcp_f32, about 1 ulp
   } else {
     st.add_grazing();
