@@ -179,9 +179,11 @@ tct_status tct_stats_read(const tct_mesh* m, tct_stats* out, int reset) {
     return TCT_E_ARG;
   }
   DeviceGuard dg(m->device);
-  unsigned long long h[kNumCounters];
+  unsigned long long rows[kCounterRows][kNumCounters], h[kNumCounters] = {0};
   TCT_HIP(hipDeviceSynchronize());
-  TCT_HIP(hipMemcpy(h, m->d_counters, sizeof(h), hipMemcpyDeviceToHost));
+  TCT_HIP(hipMemcpy(rows, m->d_counters, sizeof(rows), hipMemcpyDeviceToHost));
+  for (const auto& row : rows)
+    for (int c = 0; c < kNumCounters; ++c) h[c] += row[c];
   out->rays = (int64_t)h[kRays];
   out->segments = (int64_t)h[kSegments];
   out->zero_len = (int64_t)h[kZeroLen];
@@ -191,8 +193,8 @@ tct_status tct_stats_read(const tct_mesh* m, tct_stats* out, int reset) {
   out->failed = (int64_t)h[kFailed];
   out->grazing_fp64 = (int64_t)h[kGrazing];
   if (reset) {
-    unsigned long long z[kNumCounters] = {0};
-    TCT_HIP(hipMemcpy(m->d_counters, z, sizeof(z), hipMemcpyHostToDevice));
+    memset(rows, 0, sizeof(rows));
+    TCT_HIP(hipMemcpy(m->d_counters, rows, sizeof(rows), hipMemcpyHostToDevice));
   }
   if (out->failed > 0) {
     set_error("walk failures were counted");

@@ -500,7 +500,7 @@ tct_status mesh_build(const float* verts, int32_t nv, const int32_t* tets, int32
   }
   if ((st = upload(m->perm, &m->d_perm, &m->device_bytes)) != TCT_OK) return fail(st);
   if ((st = upload(m->inv_perm, &m->d_inv_perm, &m->device_bytes)) != TCT_OK) return fail(st);
-  std::vector<unsigned long long> zeros(kNumCounters, 0ull);
+  std::vector<unsigned long long> zeros((size_t)kCounterRows * kNumCounters, 0ull);
   if ((st = upload(zeros, &m->d_counters, &m->device_bytes)) != TCT_OK) return fail(st);
   *out = m;
   return TCT_OK;

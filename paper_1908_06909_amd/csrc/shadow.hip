@@ -192,12 +192,13 @@ __device__ __forceinline__ bool shadow_box(const ShadowArgs& A, const double* al
 __device__ __forceinline__ void flush_shadow_stats(const MeshView& M, const ShadowStats& st) {
   int vals[5] = {st.hits, st.fp64, st.exact, st.pert, st.slow};
   const int slots[5] = {kSegments, kGrazing, kExactStage, kPerturbed, kFp64Stage};
+  unsigned long long* row = counter_row(M);
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
     int x = vals[k];
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
-    if ((threadIdx.x & 63) == 0 && x) atomicAdd(M.counters + slots[k], (unsigned long long)x);
+    if ((threadIdx.x & 63) == 0 && x) atomicAdd(row + slots[k], (unsigned long long)x);
   }
 }
 

@@ -677,24 +677,29 @@ __device__ __forceinline__ void walk_ray(const MeshView& M, const Ray& r, const 
   }
 }
 
-// Adds a wavefront's counts to the mesh's counters: a shuffle reduction of
-// the lane registers, or (LdsStats) every lane's ray and step counts added to
-// the wavefront's LDS counters; then one lane per counter adds it to global
-// memory.
+// Adds a wavefront's counts to the mesh's counters with one atomic
+// instruction, a lane per counter: shuffle reductions of the lane registers
+// (of the rare events' only when the wavefront had any), or (LdsStats) every
+// lane's ray and step counts added to the wavefront's LDS counters.
+__device__ __forceinline__ int wave_sum(int x) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
+  return x;
+}
+
 __device__ __forceinline__ void flush_stats(const MeshView& M, RegStats& st, int active) {
-  int v[8] = {active, st.steps, st.zero, st.fp64, st.exact, st.pert, st.failed, st.grazing};
+  const int lane = threadIdx.x & 63;
+  const int rays = __popcll(__ballot(active)), steps = wave_sum(st.steps);
+  int v = lane == kRays ? rays : lane == kSegments ? steps : 0;
+  if (__ballot(st.zero | st.fp64 | st.exact | st.pert | st.failed | st.grazing)) {
+    const int rare[6] = {st.zero, st.fp64, st.exact, st.pert, st.failed, st.grazing};
 #pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    int x = v[c];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
-    v[c] = x;
+    for (int c = 0; c < 6; ++c) {
+      const int x = wave_sum(rare[c]);
+      if (lane == kZeroLen + c) v = x;
+    }
   }
-  if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-      if (v[c]) atomicAdd(M.counters + c, (unsigned long long)v[c]);
-  }
+  if (v) atomicAdd(counter_row(M) + lane, (unsigned long long)v);
 }
 
 __device__ __forceinline__ void flush_stats(const MeshView& M, LdsStats& st, int active) {
@@ -706,7 +711,7 @@ __device__ __forceinline__ void flush_stats(const MeshView& M, LdsStats& st, int
   if (lane < kEvents) {
     const unsigned v = st.ev[lane];
     const int slot = lane == kEvRays ? kRays : lane == kEvSteps ? kSegments : kZeroLen + lane;
-    if (v) atomicAdd(M.counters + slot, (unsigned long long)v);
+    if (v) atomicAdd(counter_row(M) + slot, (unsigned long long)v);
   }
 }
 
