@@ -284,7 +284,7 @@ __device__ int find_entry(const MeshView& M, const Ray& r, St& st) {
 // pitch an 8 x 8 tile spans about one element), so scattering every segment
 // with a global atomic makes dozens of lanes update one address at once.
 // Instead each wavefront sums its segments per tetrahedron in its own LDS
-// open-addressing table (key = tetrahedron, linear probing) and adds one
+// open-addressing table (key = tetrahedron) and adds one
 // global atomic (or, for the explicit lists, writes one record) per distinct
 // tetrahedron when it flushes the table.  The rays advance in windows of a
 // fixed number of steps and the wavefront flushes its table after each
@@ -293,9 +293,10 @@ __device__ int find_entry(const MeshView& M, const Ray& r, St& st) {
 // 64 steps on the benchmark mesh); a segment that finds no slot within
 // kLdsProbes probes goes straight to global memory.  Tables are private to a
 // wavefront, so a window ends without any block-wide barrier and each
-// wavefront runs at its own pace.  The scatters use small tables and short
-// windows (kScatterSlots, kScatterWindow: fewer registers and less LDS, four
-// wavefronts per SIMD); the explicit lists use longer windows, which make
+// wavefront runs at its own pace.  512 slots and windows of 40 steps are the
+// best of 384 / 28 .. 768 / 64 for the scatters (90 angles of the benchmark
+// 20.4 ms, against 20.8 and 20.9; coarser detectors within 3%), and keep four
+// wavefronts per SIMD; the explicit lists use longer windows, which make
 // fewer records per segment.
 //
 // The tables sum in 64-bit fixed point: LDS integer atomics run several
@@ -307,11 +308,12 @@ __device__ int find_entry(const MeshView& M, const Ray& r, St& st) {
 // term keeps an absolute error below 2^-51 2^e, far below a float32 rounding
 // of the terms that matter.  Terms below 2^51 in magnitude are converted to
 // integers with one float64 addition (round_to_i64).
-constexpr int kScatterSlots = 384;
-constexpr int kScatterWindow = 28;
+constexpr int kScatterSlots = 512;
+constexpr int kScatterWindow = 40;
 constexpr int kListSlots = 768;
 constexpr int kListWindow = 64;
 constexpr int kLdsProbes = 8;
+constexpr int kGroupBits = 2;  // slots hold aligned groups of 4 tetrahedra (table_home)
 constexpr int kBlockWaves = 4;
 
 template <int MODE>
@@ -328,16 +330,32 @@ __device__ __forceinline__ int lds_cas(lds_i32* p, int tet) {
   return expected;
 }
 
-// Multiplicative (Fibonacci) hash in 24 bits, since 24-bit multiplies run
-// at full rate and 32-bit ones at a quarter: the low 24 bits of k A, A the
-// golden-ratio fraction of 2^24, are the fractional part of k times 0.618,
-// which spreads consecutive keys over the table; its top 20 bits are scaled
-// to the table size.
+// Home slot: aligned groups of 2^kGroupBits consecutive tetrahedra keep their
+// order, the groups are hashed, and a displaced key goes on by whole groups.
+// Consecutive tetrahedra are neighbours in the mesh (internal order), so the
+// lanes of a flush, a slot each, find the tetrahedra of one cell side by side
+// and their atomics leave as one request for a line of memory, which is what
+// the scatter waits for: 90 angles of the 512 x 512 benchmark take 23.6 ms
+// with single tetrahedra hashed, 20.5 with groups of 4, 20.8 with 8 and 21.2
+// with 16 (fuller groups displace more keys), a 128 x 128 detector, whose rays
+// share few tetrahedra, 17.6, 15.9, 15.0 and 14.5.
+// The hash is multiplicative (Fibonacci) in 24 bits: the low 24 bits of k A, A
+// the golden-ratio fraction of 2^24, are the fractional part of k times 0.618,
+// which spreads consecutive groups over the table; its top 20 bits are scaled
+// to the number of groups.
 template <int kSlots>
 __device__ __forceinline__ unsigned table_home(int tet) {
   static_assert(kSlots < (1 << 12), "slot index times 2^20 must fit 32 bits");
-  const unsigned h = __umul24((unsigned)tet & 0xFFFFFFu, 0x9E3779u);
-  return (((h >> 4) & 0xFFFFFu) * (unsigned)kSlots) >> 20;
+  static_assert(kSlots % (1 << kGroupBits) == 0, "whole groups");
+  const unsigned h = __umul24(((unsigned)tet >> kGroupBits) & 0xFFFFFFu, 0x9E3779u);
+  return (((((h >> 4) & 0xFFFFFu) * (unsigned)(kSlots >> kGroupBits)) >> 20) << kGroupBits) |
+         ((unsigned)tet & ((1u << kGroupBits) - 1u));
+}
+
+template <int kSlots>
+__device__ __forceinline__ unsigned next_slot(unsigned slot) {
+  const unsigned s = slot + (1u << kGroupBits);
+  return s >= (unsigned)kSlots ? s - (unsigned)kSlots : s;
 }
 
 // x rounded to the nearest integer (ties to even), |x| < 2^51: in float64,
@@ -365,12 +383,12 @@ __device__ __forceinline__ bool lds_accumulate(lds_i32* keys, lds_i64* vals, int
   if (k != -1 && k != tet) {
     // The first probe is written out: it settles nearly every displaced key,
     // and the loop's bookkeeping then only runs when it fails.
-    slot = slot + 1 == (unsigned)kSlots ? 0u : slot + 1;
+    slot = next_slot<kSlots>(slot);
     k = lds_cas(keys + slot, tet);
     if (k != -1 && k != tet) {
 #pragma unroll 1
       for (int p = 2; p < kLdsProbes; ++p) {
-        slot = slot + 1 == (unsigned)kSlots ? 0u : slot + 1;
+        slot = next_slot<kSlots>(slot);
         k = lds_cas(keys + slot, tet);
         if (k == -1 || k == tet) break;
       }
