@@ -241,10 +241,10 @@ tct_status tct_forward(const tct_mesh* m, const tct_geom* g, const float* x, flo
                                   steps (64-bit fixed point scaled to the wavefront's largest |y_j| |P_j - S|:
                                   every term is kept to 2^-51 of it), then adds one float atomic per distinct
                                   tetrahedron to xhat */
-#define TCT_BP_GATHER 1        /* deterministic: explicit per-tetrahedron lists of the wavefronts' exact
-                                  fixed-point partial sums (one per wavefront and window of steps that crosses
-                                  the tetrahedron), each list added exactly as 128-bit integers, so the sum does
-                                  not depend on the order of the list */
+#define TCT_BP_GATHER 1        /* deterministic: the wavefronts' exact fixed-point partial sums (one per
+                                  wavefront and window of steps that crosses the tetrahedron) added exactly into
+                                  one wide integer per tetrahedron, so the sum does not depend on the order
+                                  and weak rays keep the precision of ATOMIC's on-chip sums */
 #define TCT_BP_ATOMIC_DIRECT 2 /* one float32 atomic add to xhat per segment, as in the paper */
 #define TCT_BP_FIXED 4         /* reproducible ray-driven scatter: the atomic walk with every term rounded to
                                   a multiple of 2^-s, one s per launch (terms stay below 2^K in magnitude,
@@ -264,7 +264,7 @@ tct_status tct_forward(const tct_mesh* m, const tct_geom* g, const float* x, flo
  *   mode  TCT_BP_ATOMIC, TCT_BP_ATOMIC_DIRECT, TCT_BP_GATHER or TCT_BP_SHADOW.
  *         The atomic modes sum in a run-dependent order.  GATHER and SHADOW give
  *         bitwise-identical results run to run.  GATHER allocates stream-ordered
- *         scratch and synchronises the stream once per angle chunk; SHADOW does
+ *         scratch (64 bytes per tetrahedron for up to 2^26 rays); SHADOW does
  *         not use `entry`, never synchronises, and allocates stream-ordered
  *         float64 partial sums only when the mesh has too few elements to fill
  *         the device (then angles are split into chunks summed in order). */

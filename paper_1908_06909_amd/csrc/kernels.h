@@ -11,39 +11,76 @@ enum WalkMode {
   kModeBackAtomic = 2,
   kModeCountAll = 3,
   kModeTrace = 5,
-  kModeGatherFill = 6,
+  kModeBackExact = 6,   // backprojection through the wavefront tables into exact wide sums
   kModeBackDirect = 7,  // backprojection with one global atomic per segment
   kModeEntryRstar = 8,  // entry search through the R*-tree
   kModeBackFixed = 9,   // backprojection through the block table into 64-bit fixed-point sums (reproducible)
 };
 
-// Explicit per-tetrahedron lists (TCT_BP_GATHER): records of one chunk of
-// angles, each the exact fixed-point sum m 2^-scale over the rays of one
-// wavefront and one window of steps that cross tetrahedron `tet` with
-// positive length (scale: the wavefront's, a power of two).  One 16-byte
-// record, written and moved with single 16-byte accesses.
-struct alignas(16) GatherRecord {
-  long long m;
-  int32_t tet;
-  int32_t scale;
+// Exact sums per tetrahedron (TCT_BP_GATHER).  Tetrahedron t's sum is
+// sum_l acc[l nt + t] 2^(l bits) in units of 2^-kExactUnit.  A partial sum
+// m 2^-scale (|m| < 2^57; scale at least -78 from the largest float and at most
+// kExactUnit, set by the walk) is added as balanced digits of `bits` bits to
+// consecutive words.  A ray crosses a tetrahedron once, so a word receives at
+// most one digit per ray of the launch: with bits <= 62 - ceil(log2 rays) it
+// cannot overflow.
+constexpr int kExactUnit = 120;
+struct ExactSums {
+  unsigned long long* acc;
+  int bits, words;
 };
-// The fill walk's output: counts[tet] counts the tetrahedron's records.
-// Each workgroup writes its records into one of kGatherGroups regions of
-// rec (gcap records each; the region a hash of the block index),
-// positions handed out by that region's cursor, so no single counter
-// serialises the whole launch; cursor[g] counts all of the
-// region's records, also those beyond gcap, which are not written.
-constexpr int kGatherGroups = 64;
-struct GatherOut {
-  GatherRecord* rec;
-  int32_t* counts;
-  unsigned long long* cursor;  // [kGatherGroups]
-  int64_t gcap;
-};
+
+// 36 bits up to 2^26 rays: 8 words, and a partial sum is mostly two digits.
+__host__ __device__ constexpr int exact_digit_bits(int64_t rays) {
+  int log2 = 0;
+  while (log2 < 40 && ((int64_t)1 << log2) < rays) ++log2;
+  return 62 - log2 < 36 ? 62 - log2 : 36;
+}
+
+// Words for the bits 0 .. 254 that partial sums occupy and the one above.
+__host__ __device__ constexpr int exact_words(int bits) { return (kExactUnit + 78 + 57) / bits + 1; }
+
+// The lowest digit of v, in [-2^(bits - 1), 2^(bits - 1)), and what remains:
+// v = *digit + 2^bits * (returned).
+__host__ __device__ __forceinline__ long long exact_digit(long long v, int bits, long long* digit) {
+  *digit = (long long)((unsigned long long)v << (64 - bits)) >> (64 - bits);
+  return (v >> bits) + (*digit < 0 ? 1 : 0);
+}
+
+// Calls add(word, digit) for the non-zero digits of m 2^-scale.
+template <class Add>
+__host__ __device__ __forceinline__ void exact_add(int bits, int words, int scale, long long m, const Add& add) {
+  const int pos = kExactUnit - scale < 0 ? 0 : (kExactUnit - scale > kExactUnit + 78 ? kExactUnit + 78 : kExactUnit - scale);
+  const int shift = pos % bits;
+  int w = pos / bits;
+  // The lowest digit of m 2^shift, from m's low bits; the rest is below 2^58.
+  long long d = (long long)((unsigned long long)m << (64 - bits + shift)) >> (64 - bits);
+  long long rest = (m >> (bits - shift)) + (d < 0 ? 1 : 0);
+  for (;;) {
+    if (d != 0 && w < words) add(w, d);
+    if (rest == 0 || ++w >= words) return;
+    rest = exact_digit(rest, bits, &d);
+  }
+}
+
+// The value of the accumulator whose words are word(0), word(1), ...: the
+// words' excess over a digit is carried upwards, the digits are summed in
+// float64 from the lowest up.
+template <class Word>
+__host__ __device__ __forceinline__ double exact_total(int bits, int words, const Word& word) {
+  long long carry = 0;
+  double sum = 0.0;
+  for (int l = 0; l < words; ++l) {
+    long long d;
+    carry = exact_digit(word(l) + carry, bits, &d);
+    sum += ldexp((double)d, l * bits - kExactUnit);
+  }
+  return sum + ldexp((double)carry, words * bits - kExactUnit);
+}
 
 tct_status launch_pixel_walk(int mode, const tct_mesh* m, const tct_geom* g, int a0, int na_chunk,
                              const int32_t* entry, const float* in, float* out_f32, int32_t* out_i32,
-                             const GatherOut* gather, int tile_u, hipStream_t s, int lds_table = 0,
+                             const ExactSums* exact, int tile_u, hipStream_t s, int lds_table = 0,
                              unsigned long long* acc64 = nullptr, const int* scale_exp = nullptr);
 
 tct_status backproject_atomic(const tct_mesh* m, const tct_geom* g, const float* proj, float* xhat, int accumulate,
@@ -84,8 +121,6 @@ tct_status vecset_axpy_ratio(const tct_vecset* y, const tct_vecset* x, const dou
 tct_status vecset_xpay_ratio(const tct_vecset* p, const tct_vecset* x, const double* num, const double* den,
                              hipStream_t s);
 tct_status vecset_fill(const tct_vecset* y, float v, hipStream_t s);
-
-tct_status exclusive_scan_counts(const int32_t* in, int64_t* out, int64_t n, int64_t* sums, hipStream_t s);
 
 // Host-side builders (mesh.cpp).
 tct_status mesh_build(const float* verts, int32_t nv, const int32_t* tets, int32_t nt, const int32_t* nbrs,

@@ -284,9 +284,9 @@ __device__ int find_entry(const MeshView& M, const Ray& r, St& st) {
 // pitch an 8 x 8 tile spans about one element), so scattering every segment
 // with a global atomic makes dozens of lanes update one address at once.
 // Instead each wavefront sums its segments per tetrahedron in its own LDS
-// open-addressing table (key = tetrahedron) and adds one
-// global atomic (or, for the explicit lists, writes one record) per distinct
-// tetrahedron when it flushes the table.  The rays advance in windows of a
+// open-addressing table (key = tetrahedron) and adds one global atomic (two
+// or three for the exact sums) per distinct tetrahedron when it flushes the
+// table.  The rays advance in windows of a
 // fixed number of steps and the wavefront flushes its table after each
 // window, so the table only holds the tetrahedra of one window of its ray
 // bundle (an 8 x 8 bundle meets about 170 tetrahedra per 32 steps, 300 per
@@ -296,31 +296,22 @@ __device__ int find_entry(const MeshView& M, const Ray& r, St& st) {
 // wavefront runs at its own pace.  512 slots and windows of 40 steps are the
 // best of 384 / 28 .. 768 / 64 for the scatters (90 angles of the benchmark
 // 20.4 ms, against 20.8 and 20.9; coarser detectors within 3%), and keep four
-// wavefronts per SIMD; the explicit lists use longer windows, which make
-// fewer records per segment.
+// wavefronts per SIMD.
 //
 // The tables sum in 64-bit fixed point: LDS integer atomics run several
 // times faster than float ones on this chip.  Each term t = L y_j |d| is
 // rounded to a multiple of 2^-50 2^e, 2^e the next power of two above the
 // wavefront's largest |y_j| |d|, and at most 64 terms (one per ray of the
 // wavefront) meet in a slot per window, so the integer sum stays below 2^56
-// and is exact; the flush converts it back (or records it as it is).  Every
+// and is exact; the flush converts it back (or adds it as it is).  Every
 // term keeps an absolute error below 2^-51 2^e, far below a float32 rounding
 // of the terms that matter.  Terms below 2^51 in magnitude are converted to
 // integers with one float64 addition (round_to_i64).
 constexpr int kScatterSlots = 512;
 constexpr int kScatterWindow = 40;
-constexpr int kListSlots = 768;
-constexpr int kListWindow = 64;
 constexpr int kLdsProbes = 8;
 constexpr int kGroupBits = 2;  // slots hold aligned groups of 4 tetrahedra (table_home)
 constexpr int kBlockWaves = 4;
-
-template <int MODE>
-struct TableShape {
-  static constexpr int slots = MODE == kModeGatherFill ? kListSlots : kScatterSlots;
-  static constexpr int window = MODE == kModeGatherFill ? kListWindow : kScatterWindow;
-};
 
 // Claims an empty slot (-1) for key `tet`; returns the key found there before.
 __device__ __forceinline__ int lds_cas(lds_i32* p, int tet) {
@@ -399,20 +390,11 @@ __device__ __forceinline__ bool lds_accumulate(lds_i32* keys, lds_i64* vals, int
   return true;
 }
 
-// The record region of this workgroup: a multiplicative hash of the block
-// index, so that every region gets a fair share of the detector's central
-// (long-ray) and outer blocks whatever the tiling.
-__device__ __forceinline__ unsigned gather_group() {
-  static_assert(kGatherGroups == 64, "the region is the hash's top 6 bits");
-  return ((unsigned)blockIdx.x * 2654435761u) >> 26;
-}
-
-// Record number p of this workgroup's region.
-__device__ __forceinline__ void gather_record(const GatherOut& g, int64_t p, int tet, int scale, long long m) {
-  if (p < g.gcap) g.rec[(int64_t)gather_group() * g.gcap + p] = GatherRecord{m, tet, scale};
-  // Counted here, where the atomic's latency hides behind the walk (a
-  // separate pass over the records took three times as long).
-  atomicAdd(g.counts + tet, 1);
+// Adds the partial sum m 2^-scale to tetrahedron tet's exact sum.
+__device__ __forceinline__ void add_exact(const ExactSums& g, int nt, int tet, int scale, long long m) {
+  exact_add(g.bits, g.words, scale, m, [&](int w, long long d) {
+    atomicAdd(g.acc + (int64_t)w * nt + tet, (unsigned long long)d);
+  });
 }
 
 template <int MODE>
@@ -420,7 +402,7 @@ struct WalkOut {
   // FWD
   const float* x = nullptr;
   double acc = 0.0;
-  // BWD / GATHER_FILL: weight = y_j * |d|; the table walks hold it times
+  // BWD: weight = y_j * |d|; the table walks hold it times
   // lds_scale, so that a segment's fixed-point term is one product away
   float weight = 0.f;
   float* xhat = nullptr;
@@ -428,8 +410,7 @@ struct WalkOut {
   lds_i64* lds_vals = nullptr;
   float lds_scale = 1.f;  // fixed-point scale of the table (a power of two)
   unsigned long long* acc64 = nullptr;  // fixed-point result (reproducible mode), else null
-  // GATHER_FILL: records of the explicit lists; key of the current window
-  GatherOut gather{};
+  ExactSums exact{};  // exact sums per tetrahedron
   int scale_exp = 0;  // log2 of lds_scale
   // TRACE output cursor
   int32_t* out_tet = nullptr;
@@ -485,7 +466,7 @@ __constant__ LocRemap kLocRemap = make_loc_remap();
 // The walks that look the remap up in LDS (a read per step in place of about
 // fifteen vector instructions); the others keep the bit-parallel remap.
 constexpr bool loc_table(int MODE) {
-  return MODE == kModeForward || MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeGatherFill;
+  return MODE == kModeForward || MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeBackExact;
 }
 
 __shared__ __align__(4) unsigned char s_loc_remap[kLocRemapEntries];
@@ -608,19 +589,18 @@ __device__ __forceinline__ bool walk_step(const MeshView& M, const Ray& r, const
   if (dt == 0.f) st.add_zero();
   if constexpr (MODE == kModeForward) {
     o.acc = fma((double)dt, (double)w.xcur, o.acc);  // the product is exact
-  } else if constexpr (MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeGatherFill) {
+  } else if constexpr (MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeBackExact) {
     // Every segment goes into the table, a zero-length one as 0 (dt is never
     // negative or NaN after the clamp): adding zero costs less than a branch
     // per step, and the step's claim is then consumed on every path.
     const float v = dt * o.weight;  // in units of 2^-scale_exp
     const long long m = round_to_i64(v);
-    if (!lds_accumulate<TableShape<MODE>::slots>(o.lds_keys, o.lds_vals, tet, m,
+    if (!lds_accumulate<kScatterSlots>(o.lds_keys, o.lds_vals, tet, m,
                                                  w.home, w.claim)) {
       if constexpr (MODE == kModeBackFixed) {
         atomicAdd(o.acc64 + tet, (unsigned long long)m);
-      } else if constexpr (MODE == kModeGatherFill) {
-        const int64_t p = (int64_t)atomicAdd(o.gather.cursor + gather_group(), 1ull);
-        gather_record(o.gather, p, tet, o.scale_exp, m);
+      } else if constexpr (MODE == kModeBackExact) {
+        add_exact(o.exact, M.nt, tet, o.scale_exp, m);
       } else {
         unsafeAtomicAdd(o.xhat + tet, ldexpf(v, -o.scale_exp));
       }
@@ -676,8 +656,8 @@ __device__ __forceinline__ bool walk_step(const MeshView& M, const Ray& r, const
   w.tet = packed >> 2;
   // Table walks claim the new tetrahedron's home slot now; the old key comes
   // back while the next step computes, and is needed only at its end.
-  if constexpr (MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeGatherFill) {
-    w.home = table_home<TableShape<MODE>::slots>(w.tet);
+  if constexpr (MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeBackExact) {
+    w.home = table_home<kScatterSlots>(w.tet);
     w.claim = lds_cas(o.lds_keys + w.home, w.tet);
   }
   if constexpr (MODE == kModeForward) w.xcur = o.x[w.tet];
@@ -760,7 +740,7 @@ struct BlockIO {
   const float* in;
   float* out_f32;
   int32_t* out_i32;
-  GatherOut gather;  // kModeGatherFill
+  ExactSums exact;  // kModeBackExact
   int lds_table;
   unsigned long long* acc64;  // kModeBackFixed: fixed-point sums [nt]
   const int* scale_exp;       // kModeBackFixed: log2 of their scale
@@ -773,7 +753,7 @@ struct BlockIO {
 //   kModeBackAtomic: xhat[i] += a_ij y_j through the block's LDS table
 //   kModeBackFixed:  acc64[i] += a_ij y_j 2^scale_exp, exact integer sums
 //   kModeBackDirect: xhat[i] += a_ij y_j, one global atomic per segment
-//   kModeGatherFill: records of the explicit per-tetrahedron lists
+//   kModeBackExact: exact sums += a_ij y_j
 // Every thread of the block must call it.
 // kCached: every ray's entry face comes from io.entry (the launch has an
 // entry cache), so the kernel carries no tree search.
@@ -784,13 +764,13 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
   int a, i, j;
   bool active = tile_ray(G, tm, block, threadIdx.x, a0, na_chunk, &a, &i, &j);
   // The scatter walks keep their rare counts in LDS, the others in registers.
-  constexpr bool kTable = MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeGatherFill;
+  constexpr bool kTable = MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeBackExact;
   using St = typename std::conditional<kTable, LdsStats, RegStats>::type;
   __shared__ unsigned s_ev[kTable ? kBlockWaves * kEvents : 1];
   St st(kTable ? wave_counters(s_ev) : nullptr);
   if constexpr (kTable) {
     const int lane = threadIdx.x & 63;
-    constexpr int kSlots = TableShape<MODE>::slots, kWindow = TableShape<MODE>::window;
+    constexpr int kSlots = kScatterSlots, kWindow = kScatterWindow;
     lds_i32* keys = (lds_i32*)tkeys + kSlots * wave_in_block();
     lds_i64* vals = (lds_i64*)tvals + kSlots * wave_in_block();
     for (int k = lane; k < kSlots; k += 64) {
@@ -830,7 +810,7 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
       o.lds_scale = ldexpf(1.0f, o.scale_exp);
       o.acc64 = io.acc64;
     } else {
-      if constexpr (MODE == kModeGatherFill) o.gather = io.gather;
+      if constexpr (MODE == kModeBackExact) o.exact = io.exact;
       // Fixed-point scale from the wavefront's largest ray weight (a max over
       // the float bits, which order like the values for non-negative floats).
       __shared__ unsigned s_wmax[kBlockWaves];
@@ -874,45 +854,20 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
       // every add of the window.
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      if constexpr (MODE == kModeGatherFill) {
-        // One record per occupied slot, at consecutive positions reserved
-        // with one atomic for the wavefront.  (Slots claimed ahead by a
-        // window's last step hold zero and are only cleared.)
-        unsigned total = 0;
-        for (int k = lane; k < kSlots; k += 64) total += __popcll(__ballot(keys[k] >= 0 && vals[k] != 0));
-        unsigned long long base = 0;
-        if (lane == 0 && total)
-          base = atomicAdd(o.gather.cursor + gather_group(), (unsigned long long)total);
-        base = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32) |
-               (unsigned)__builtin_amdgcn_readfirstlane((int)base);
-        for (int k = lane; k < kSlots; k += 64) {
-          const int key = keys[k];
+      for (int k = lane; k < kSlots; k += 64) {
+        const int key = keys[k];
+        if (key >= 0) {
           const long long v = vals[k];
-          const unsigned long long m = __ballot(key >= 0 && v != 0);
-          if (key >= 0) {
-            if (v != 0) {
-              const int64_t p = (int64_t)base + __popcll(m & ((1ull << lane) - 1ull));
-              gather_record(o.gather, p, key, o.scale_exp, v);
-            }
-            keys[k] = -1;
-            vals[k] = 0;
+          if (v != 0) {
+            if constexpr (MODE == kModeBackFixed)
+              atomicAdd(io.acc64 + key, (unsigned long long)v);
+            else if constexpr (MODE == kModeBackExact)
+              add_exact(o.exact, M.nt, key, o.scale_exp, v);
+            else
+              unsafeAtomicAdd(io.out_f32 + key, (float)ldexp((double)v, -o.scale_exp));
           }
-          base += __popcll(m);
-        }
-      } else {
-        for (int k = lane; k < kSlots; k += 64) {
-          const int key = keys[k];
-          if (key >= 0) {
-            const long long v = vals[k];
-            if (v != 0) {
-              if constexpr (MODE == kModeBackFixed)
-                atomicAdd(io.acc64 + key, (unsigned long long)v);
-              else
-                unsafeAtomicAdd(io.out_f32 + key, (float)ldexp((double)v, -o.scale_exp));
-            }
-            keys[k] = -1;
-            vals[k] = 0;
-          }
+          keys[k] = -1;
+          vals[k] = 0;
         }
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -963,9 +918,9 @@ template <int MODE, bool kCached>
 __global__ __launch_bounds__(256, 4) void pixel_walk_kernel(MeshView M, GeomView G, TileMap tm, int a0, int na_chunk,
                                                          BlockIO io) {
   if constexpr (loc_table(MODE)) load_loc_remap();
-  if constexpr (MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeGatherFill) {
-    __shared__ int tkeys[kBlockWaves * TableShape<MODE>::slots];
-    __shared__ long long tvals[kBlockWaves * TableShape<MODE>::slots];
+  if constexpr (MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeBackExact) {
+    __shared__ int tkeys[kBlockWaves * kScatterSlots];
+    __shared__ long long tvals[kBlockWaves * kScatterSlots];
     walk_block<MODE, false, kCached>(M, G, tm, xcd_block(blockIdx.x, gridDim.x), a0, na_chunk, io, tkeys, tvals);
   } else {
     walk_block<MODE, false, kCached>(M, G, tm, xcd_block(blockIdx.x, gridDim.x), a0, na_chunk, io, nullptr,
@@ -1215,8 +1170,8 @@ __global__ __launch_bounds__(256, 4) void batch_walk_kernel(const BatchDesc* __r
     io.out_f32 = outs[d.user];
     io.lds_table = d.lds_table;
     if constexpr (MODE == kModeBackAtomic) {
-      __shared__ int tkeys[kBlockWaves * TableShape<MODE>::slots];
-      __shared__ long long tvals[kBlockWaves * TableShape<MODE>::slots];
+      __shared__ int tkeys[kBlockWaves * kScatterSlots];
+      __shared__ long long tvals[kBlockWaves * kScatterSlots];
       walk_block<MODE, true, true>(d.M, d.G, d.tm, block, 0, d.G.na, io, tkeys, tvals);
     } else {
       walk_block<MODE, true, true>(d.M, d.G, d.tm, block, 0, d.G.na, io, nullptr, nullptr);
@@ -1342,7 +1297,7 @@ int64_t pixel_walk_waves(const tct_geom* g, int na_chunk, int tile_u) {
 
 tct_status launch_pixel_walk(int mode, const tct_mesh* m, const tct_geom* g, int a0, int na_chunk,
                              const int32_t* entry, const float* in, float* out_f32, int32_t* out_i32,
-                             const GatherOut* gather, int tile_u, hipStream_t s, int lds_table,
+                             const ExactSums* exact, int tile_u, hipStream_t s, int lds_table,
                              unsigned long long* acc64, const int* scale_exp) {
   MeshView M = m->view();
   GeomView G = g->view();
@@ -1353,7 +1308,7 @@ tct_status launch_pixel_walk(int mode, const tct_mesh* m, const tct_geom* g, int
     set_error("too many rays in one launch");
     return TCT_E_ARG;
   }
-  BlockIO io{entry, in, out_f32, out_i32, gather ? *gather : GatherOut{}, lds_table, acc64, scale_exp};
+  BlockIO io{entry, in, out_f32, out_i32, exact ? *exact : ExactSums{}, lds_table, acc64, scale_exp};
   dim3 grid((unsigned)blocks), block(256);
 #define TCT_LAUNCH(MODE_)                                                                              \
   do {                                                                                                 \
@@ -1381,8 +1336,8 @@ tct_status launch_pixel_walk(int mode, const tct_mesh* m, const tct_geom* g, int
     case kModeBackFixed:
       TCT_LAUNCH(kModeBackFixed);
       break;
-    case kModeGatherFill:
-      TCT_LAUNCH(kModeGatherFill);
+    case kModeBackExact:
+      TCT_LAUNCH(kModeBackExact);
       break;
     default:
       set_error("bad walk mode");
