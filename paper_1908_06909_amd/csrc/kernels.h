@@ -17,6 +17,15 @@ enum WalkMode {
   kModeBackFixed = 9,   // backprojection through the block table into 64-bit fixed-point sums (reproducible)
 };
 
+// What the reproducible scatter's scale follows from (TCT_BP_FIXED): the
+// largest |y_j| of the launch, as float bits in device memory, a bound on the
+// rays' length and the bits a term may have.
+struct FixedScale {
+  const unsigned* max_bits;
+  float max_dlen;
+  int bits;
+};
+
 // Exact sums per tetrahedron (TCT_BP_GATHER).  Tetrahedron t's sum is
 // sum_l acc[l nt + t] 2^(l bits) in units of 2^-kExactUnit.  A partial sum
 // m 2^-scale (|m| < 2^57; scale at least -78 from the largest float and at most
@@ -81,7 +90,7 @@ __host__ __device__ __forceinline__ double exact_total(int bits, int words, cons
 tct_status launch_pixel_walk(int mode, const tct_mesh* m, const tct_geom* g, int a0, int na_chunk,
                              const int32_t* entry, const float* in, float* out_f32, int32_t* out_i32,
                              const ExactSums* exact, int tile_u, hipStream_t s, int lds_table = 0,
-                             unsigned long long* acc64 = nullptr, const int* scale_exp = nullptr);
+                             unsigned long long* acc64 = nullptr, const FixedScale* scale = nullptr);
 
 tct_status backproject_atomic(const tct_mesh* m, const tct_geom* g, const float* proj, float* xhat, int accumulate,
                               const int32_t* entry, int tile_u, int lds_table, hipStream_t s);

@@ -743,8 +743,17 @@ struct BlockIO {
   ExactSums exact;  // kModeBackExact
   int lds_table;
   unsigned long long* acc64;  // kModeBackFixed: fixed-point sums [nt]
-  const int* scale_exp;       // kModeBackFixed: log2 of their scale
+  FixedScale scale;           // kModeBackFixed: gives their scale
 };
+
+// log2 of the reproducible scatter's scale: 2^e, the power of two above the
+// largest |y_j| |d|, becomes 2^bits.
+__device__ __forceinline__ int fixed_scale_exp(const FixedScale& f) {
+  const float w = __uint_as_float(*f.max_bits) * f.max_dlen;
+  int e = 0;
+  if (w > 0.f && w < INFINITY) (void)frexpf(w, &e);
+  return min(max(f.bits - e, -120), 120);
+}
 
 // Walk the rays of pixel block `block` (of angles [a0, a0 + na_chunk)).
 //   kModeEntry:      out_i32[rid] = entry face (or -1)
@@ -806,7 +815,7 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
     if constexpr (MODE == kModeBackFixed) {
       // One scale for the whole launch, so that every sum is an exact
       // integer whatever the order of the additions.
-      o.scale_exp = *io.scale_exp;
+      o.scale_exp = __builtin_amdgcn_readfirstlane(fixed_scale_exp(io.scale));
       o.lds_scale = ldexpf(1.0f, o.scale_exp);
       o.acc64 = io.acc64;
     } else {
@@ -1227,35 +1236,43 @@ __global__ __launch_bounds__(256) void list_walk_kernel(MeshView M, GeomView G, 
   flush_stats(M, st, active ? 1 : 0);
 }
 
-// Reproducible scatter: the largest |y_j| of the launch (as float bits,
-// which order like the values for non-negative floats), the scale exponent
-// derived from it, the zeroed integer sums and their conversion at the end.
-__global__ void max_abs_kernel(const float* y, int64_t n, unsigned* out) {
+// Reproducible scatter: clears the integer sums and the largest |y_j|, finds
+// the latter (as float bits, which order like the values for non-negative
+// floats), and converts the sums at the end.
+__global__ void fixed_clear_kernel(unsigned* max_bits, unsigned long long* acc, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) *max_bits = 0u;
+  if (i < n) acc[i] = 0ull;
+}
+
+// Four loads in flight a lane, one atomic a block, and at most 1024 blocks:
+// the atomics on the one word are served one after the other, about 10 ns
+// each (an atomic per wavefront of 4096 blocks: 188 us for 4.6M values).
+constexpr int kMaxBlocks = 1024;
+__global__ __launch_bounds__(256) void max_abs_kernel(const float* y, int64_t n, unsigned* out) {
+  __shared__ float s_m[4];
+  const int64_t stride = (int64_t)gridDim.x * 256;
   float m = 0.f;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    m = fmaxf(m, fabsf(y[i]));
+  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  for (; i + 3 * stride < n; i += 4 * stride)
+    m = fmaxf(m, fmaxf(fmaxf(fabsf(y[i]), fabsf(y[i + stride])),
+                       fmaxf(fabsf(y[i + 2 * stride]), fabsf(y[i + 3 * stride]))));
+  for (; i < n; i += stride) m = fmaxf(m, fabsf(y[i]));
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-  if ((threadIdx.x & 63) == 0) atomicMax(out, __float_as_uint(m));
+  if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    m = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]));
+    if (m > 0.f) atomicMax(out, __float_as_uint(m));
+  }
 }
 
-__global__ void fixed_scale_kernel(const unsigned* max_bits, float max_dlen, int K, int* exp_out) {
-  const float w = __uint_as_float(*max_bits) * max_dlen;
-  int e = 0;
-  if (w > 0.f && w < INFINITY) (void)frexpf(w, &e);
-  *exp_out = min(max(K - e, -120), 120);
-}
-
-__global__ void zero_u64_kernel(unsigned long long* p, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0ull;
-}
-
-__global__ void fixed_finish_kernel(const unsigned long long* acc, const int* scale_exp, float* xhat, int n,
+__global__ void fixed_finish_kernel(const unsigned long long* acc, FixedScale scale, float* xhat, int n,
                                     int accumulate) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const double v = ldexp((double)(long long)acc[i], -*scale_exp);
+  const double v = ldexp((double)(long long)acc[i], -fixed_scale_exp(scale));
   xhat[i] = accumulate ? (float)((double)xhat[i] + v) : (float)v;
 }
 
@@ -1298,7 +1315,7 @@ int64_t pixel_walk_waves(const tct_geom* g, int na_chunk, int tile_u) {
 tct_status launch_pixel_walk(int mode, const tct_mesh* m, const tct_geom* g, int a0, int na_chunk,
                              const int32_t* entry, const float* in, float* out_f32, int32_t* out_i32,
                              const ExactSums* exact, int tile_u, hipStream_t s, int lds_table,
-                             unsigned long long* acc64, const int* scale_exp) {
+                             unsigned long long* acc64, const FixedScale* scale) {
   MeshView M = m->view();
   GeomView G = g->view();
   TileMap tm = make_tiles(G, tile_u);
@@ -1308,7 +1325,8 @@ tct_status launch_pixel_walk(int mode, const tct_mesh* m, const tct_geom* g, int
     set_error("too many rays in one launch");
     return TCT_E_ARG;
   }
-  BlockIO io{entry, in, out_f32, out_i32, exact ? *exact : ExactSums{}, lds_table, acc64, scale_exp};
+  BlockIO io{entry, in, out_f32, out_i32, exact ? *exact : ExactSums{}, lds_table, acc64,
+             scale ? *scale : FixedScale{}};
   dim3 grid((unsigned)blocks), block(256);
 #define TCT_LAUNCH(MODE_)                                                                              \
   do {                                                                                                 \
@@ -1390,8 +1408,8 @@ tct_status backproject_atomic(const tct_mesh* m, const tct_geom* g, const float*
 // magnitude (within the range of the walk's float-to-integer rounding) and
 // no tetrahedron's sum of at most `rays` terms can reach 2^62.  The block
 // tables and the global sums then add integers, exactly, in any order.
-// Scratch layout of the reproducible scatter: [max |y| bits, scale exponent,
-// pad to 256 B][nt int64 sums].
+// Scratch layout of the reproducible scatter: [max |y| bits, pad to 256
+// B][nt int64 sums].
 static size_t fixed_scratch_bytes(int nt) { return 256 + 8 * (size_t)nt; }
 
 static tct_status backproject_fixed_in(const tct_mesh* m, const tct_geom* g, const float* proj, float* xhat,
@@ -1419,25 +1437,22 @@ static tct_status backproject_fixed_in(const tct_mesh* m, const tct_geom* g, con
   int bits = 1;
   while (bits < 62 && ((int64_t)1 << bits) < nrays) ++bits;
   const int K = std::min(50, 62 - bits);
-  unsigned long long* acc = nullptr;
   unsigned* max_bits = (unsigned*)scratch;
-  int* scale_exp = (int*)(scratch + 4);
-  acc = (unsigned long long*)(scratch + 256);
-  hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, (unsigned long long*)scratch, (int64_t)1);
-  hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)((m->nt + 255) / 256)), dim3(256), 0, s, acc, (int64_t)m->nt);
+  unsigned long long* acc = (unsigned long long*)(scratch + 256);
+  hipLaunchKernelGGL(fixed_clear_kernel, dim3((unsigned)((m->nt + 255) / 256)), dim3(256), 0, s, max_bits, acc,
+                     (int64_t)m->nt);
   const float* y = proj + per_angle * a_begin;
-  const unsigned mgrid = (unsigned)std::min<int64_t>(4096, (nrays + 255) / 256);
+  const unsigned mgrid = (unsigned)std::min<int64_t>(kMaxBlocks, (nrays + 1023) / 1024);
   hipLaunchKernelGGL(max_abs_kernel, dim3(mgrid), dim3(256), 0, s, y, nrays, max_bits);
-  hipLaunchKernelGGL(fixed_scale_kernel, dim3(1), dim3(1), 0, s, (const unsigned*)max_bits,
-                     (float)(dmax * 1.0001), K, scale_exp);
+  const FixedScale scale{max_bits, (float)(dmax * 1.0001), K};
   hipError_t e = hipGetLastError();
   tct_status st = TCT_OK;
   if (e == hipSuccess)
     st = launch_pixel_walk(kModeBackFixed, m, g, a_begin, a_count, entry, proj, xhat, nullptr, nullptr, tile_u,
-                           s, 1, acc, scale_exp);
+                           s, 1, acc, &scale);
   if (e == hipSuccess && st == TCT_OK) {
     hipLaunchKernelGGL(fixed_finish_kernel, dim3((unsigned)((m->nt + 255) / 256)), dim3(256), 0, s,
-                       (const unsigned long long*)acc, (const int*)scale_exp, xhat, m->nt, accumulate);
+                       (const unsigned long long*)acc, scale, xhat, m->nt, accumulate);
     e = hipGetLastError();
   }
   if (e != hipSuccess) return hip_fail(e, "reproducible scatter launch");
