@@ -56,6 +56,7 @@ struct MeshView {
   int nb;
   unsigned long long* counters;  // [kCounterRows][kNumCounters], see counter_row
   float extent;                  // largest |coordinate| of any node
+  float edge_max;                // largest |coordinate difference| along any edge, rounded to float32
   // tetxyz[3 t + 0..2]: the four vertices of tetrahedron t as 12 floats
   // (v0.xyz v1.xyz v2.xyz v3.xyz), ordered so that
   // det[v1 - v0, v2 - v0, v3 - v0] > 0.
@@ -165,6 +166,7 @@ struct tct_mesh {
   std::vector<int32_t> inv_perm;   // user -> internal
   std::vector<int32_t> user_nbrs;  // [nt][4] user numbering
   float lo[3], hi[3];              // bounding box of the nodes
+  float edge_max = 0.f;            // largest |coordinate difference| along any edge
   float4* d_faces = nullptr;
   float4* d_bfaces = nullptr;
   float4* d_tetxyz = nullptr;
@@ -196,6 +198,7 @@ struct tct_mesh {
     v.tetnbr = d_tetnbr;
     v.rstar = d_rstar;
     v.rstar_faces = d_rstar_faces;
+    v.edge_max = edge_max;
     v.extent = 0.f;
     for (int k = 0; k < 3; ++k) v.extent = std::max(v.extent, std::max(std::fabs(lo[k]), std::fabs(hi[k])));
     return v;

@@ -476,6 +476,8 @@ tct_status mesh_build(const float* verts, int32_t nv, const int32_t* tets, int32
     float c[12];
     for (int k = 0; k < 4; ++k)
       for (int x = 0; x < 3; ++x) c[3 * k + x] = P(idx[k])[x];
+    for (int k = 0; k < 12; ++k)
+      for (int j = k + 3; j < 12; j += 3) m->edge_max = std::max(m->edge_max, std::fabs(c[k] - c[j]));
     for (int w = 0; w < 3; ++w) tetxyz[3 * (size_t)i + w] = make_float4(c[4 * w], c[4 * w + 1], c[4 * w + 2], c[4 * w + 3]);
   }
   tct_status st;

@@ -49,14 +49,13 @@ typedef __attribute__((address_space(3))) long long lds_i64;
 // The wavefront index within the block, as a wave-uniform (scalar) value.
 __device__ __forceinline__ int wave_in_block() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
-// Walk statistics, in two forms with the same interface.  RegStats keeps
-// every count in a lane register (the forward, trace and entry walks, where
-// a register costs nothing and a branch per step would).  LdsStats keeps
-// only the step count per lane and adds the rare events (zero-length
-// passages, float64 and exact sign evaluations, perturbed ties, failures,
-// float64 crossings) straight to the wavefront's own counters in LDS, which
-// frees the registers the scatter walks need for their table.  flush_stats
-// adds either to the mesh's counters once per wavefront.
+// Walk statistics, in two forms with the same interface.  RegStats keeps its
+// counts in lane registers (the entry searches).  LdsStats adds the rare
+// events (zero-length passages, float64 and exact sign evaluations, perturbed
+// ties, failures, float64 crossings) straight to the wavefront's own counters
+// in LDS, in branches that the step loop skips; the walks count their steps
+// per wavefront, in a scalar register.  flush_stats adds either to the mesh's
+// counters once per wavefront.
 enum Event { kEvZero = 0, kEvFp64, kEvExact, kEvPert, kEvFailed, kEvGrazing, kEvRays, kEvSteps, kEvents };
 
 __device__ __forceinline__ void lds_add_u32(lds_u32* p, unsigned v) {
@@ -64,7 +63,7 @@ __device__ __forceinline__ void lds_add_u32(lds_u32* p, unsigned v) {
 }
 
 struct RegStats {
-  int steps = 0, zero = 0, fp64 = 0, exact = 0, pert = 0, failed = 0, grazing = 0;
+  int zero = 0, fp64 = 0, exact = 0, pert = 0, failed = 0, grazing = 0;
   __device__ __forceinline__ explicit RegStats(lds_u32*) {}
   __device__ __forceinline__ void add_zero() { zero++; }
   __device__ __forceinline__ void add_grazing() { grazing++; }
@@ -75,7 +74,6 @@ struct RegStats {
 };
 
 struct LdsStats {
-  int steps = 0;
   lds_u32* ev;  // this wavefront's kEvents counters in LDS
   __device__ __forceinline__ explicit LdsStats(lds_u32* wave_counters) : ev(wave_counters) {}
   __device__ __forceinline__ void add_zero() { lds_add_u32(ev + kEvZero, 1u); }
@@ -84,6 +82,8 @@ struct LdsStats {
   __device__ __forceinline__ void add_exact() { lds_add_u32(ev + kEvExact, 1u); }
   __device__ __forceinline__ void add_pert() { lds_add_u32(ev + kEvPert, 1u); }
   __device__ __forceinline__ void add_failed() { lds_add_u32(ev + kEvFailed, 1u); }
+  // A ray that fails in a step has not made it.
+  __device__ __forceinline__ void take_back_step() { lds_add_u32(ev + kEvSteps, ~0u); }
 };
 
 // The calling wavefront's event counters in the block's table `all`
@@ -424,25 +424,21 @@ struct WalkOut {
 // Walk state between steps: the entry face as three vertex slots, the
 // fourth vertex v, the current tetrahedron and the ray parameter where the
 // ray entered it.  `loc` holds the local indices (0..3 within the current
-// tetrahedron) of slots 0, 1, 2 and of v: in four 2-bit fields of one byte
-// for the walks that remap it through the LDS table (loc_table), in four
-// 4-bit fields for the bit-parallel remap of the others.
+// tetrahedron) of slots 0, 1, 2 and of v in four 2-bit fields of one byte.
 //
 // Crossing face f (the face opposite local vertex f) into a neighbour whose
 // opposite vertex has local index `back` there, the three shared vertices
 // keep their order: local indices are sorted the same way in both elements,
 // so a shared vertex of rank r among the face's vertices has local index
-// r + (r >= back) in the neighbour, with r = p - (p > f).  walk_step applies
-// this to all four fields at once.
+// r + (r >= back) in the neighbour, with r = p - (p > f).  A table gives the
+// neighbour's byte (LocRemap).
 struct WalkState {
   float3 a0, a1, a2, v;
-  int tet;
+  int packed;  // (tetrahedron << 2) | 0..3, as in its predecessor's record; negative: the ray has ended
   unsigned loc;
   double s_in;  // ray parameter where the ray entered the current tetrahedron
-  float xcur;  // forward projection: x of the current tetrahedron
   int claim;   // table walks: old key returned by the claim of the tetrahedron's home slot
   unsigned home;  // table walks: that home slot, kept from the claim for the step's accumulation
-  int steps;
   // Every ray of the wavefront ends beyond the mesh (ends_beyond_mesh), so
   // segments need no clamp at the end point; the same for the whole
   // wavefront, hence a scalar branch per step.
@@ -450,7 +446,8 @@ struct WalkState {
 };
 
 // Local-index remap as a table of loc_remap_entry (common.h), one byte per
-// (loc, k, back), copied into each block's LDS by the walks that use it.
+// (loc, k, back), copied into each block's LDS: a read per step, in place of
+// about fifteen vector instructions.
 struct alignas(4) LocRemap {
   unsigned char v[kLocRemapEntries];
 };
@@ -462,12 +459,6 @@ constexpr LocRemap make_loc_remap() {
 }
 
 __constant__ LocRemap kLocRemap = make_loc_remap();
-
-// The walks that look the remap up in LDS (a read per step in place of about
-// fifteen vector instructions); the others keep the bit-parallel remap.
-constexpr bool loc_table(int MODE) {
-  return MODE == kModeForward || MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeBackExact;
-}
 
 __shared__ __align__(4) unsigned char s_loc_remap[kLocRemapEntries];
 
@@ -487,12 +478,8 @@ __device__ __forceinline__ void walk_start(const MeshView& M, const Ray& r, cons
   w.far = far;
   const float4* bq = M.bfaces + 4 * (size_t)entry;
   float4 q0 = bq[0], q1 = bq[1], q2 = bq[2], q3 = bq[3];
-  w.tet = __float_as_int(q0.w);
-  unsigned lp = (unsigned)__float_as_int(q1.w);
-  if constexpr (loc_table(MODE))
-    w.loc = lp & 0xFFu;
-  else
-    w.loc = (lp & 3u) | ((lp & 12u) << 2) | ((lp & 48u) << 4) | ((lp & 192u) << 6);
+  w.packed = __float_as_int(q0.w) << 2;
+  w.loc = (unsigned)__float_as_int(q1.w) & 0xFFu;
   w.a0 = make_float3(q0.x, q0.y, q0.z);
   w.a1 = make_float3(q1.x, q1.y, q1.z);
   w.a2 = make_float3(q2.x, q2.y, q2.z);
@@ -506,103 +493,111 @@ __device__ __forceinline__ void walk_start(const MeshView& M, const Ray& r, cons
   // drift by a rounding of the parameter per step.
   const double s_in = crossing_s_fp64(q.S(), q.P(), w.a0, w.a1, w.a2);
   w.s_in = fmin(fmax(s_in, -0.5), 0.5);
-  w.xcur = 0.f;
-  if constexpr (MODE == kModeForward) w.xcur = o.x[w.tet];
-  w.steps = 0;
 }
 
 // One step: leave the current tetrahedron, apply the mode's action for its
-// segment, move to the neighbour.  Returns false once the ray has left the
-// mesh (or the walk failed).  kLimit: the step bounds the walk itself (a ray
-// never crosses more than nt elements); the windowed walks bound it once per
-// window instead.
-template <int MODE, bool kLimit = true, class Src, class St>
-__device__ __forceinline__ bool walk_step(const MeshView& M, const Ray& r, const Src& q, WalkState& w,
+// segment, move to the neighbour (w.packed is negative once the ray has left
+// the mesh or the walk failed).  The caller bounds the number of steps (a ray
+// never crosses more than nt elements).
+//
+// The loop is bound by the rate at which vector instructions issue (neither
+// more wavefronts nor fewer change its time), and on this chip additions,
+// products and moves issue in about half the time of selects, fused
+// multiply-adds and float64 operations.  Hence the signs as wavefront masks,
+// combined in scalar registers; edges subtracted anew rather than selected;
+// and one bound for all edges of the mesh in place of each step's own.  96
+// vector instructions a step instead of 129: 90 angles of the benchmark
+// forward 15.1 -> 13.3 ms, atomic backprojection 20.2 -> 18.1 (from a mesh
+// seen by few rays, where memory is the bound, as before: 6.4 and 15.8).
+template <int MODE, class Src, class St>
+__device__ __forceinline__ void walk_step(const MeshView& M, const Ray& r, const Src& q, WalkState& w,
                                           WalkOut<MODE>& o, St& st) {
-  if (kLimit && w.steps > M.nt) {
-    st.add_failed();
-    st.steps += w.steps;
-    return false;
-  }
+  constexpr bool kTable = MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeBackExact;
   const float3 v = w.v;
+  const int tet = w.packed >> 2;
+  float x = 0.f;  // (issued first, needed last)
+  if constexpr (MODE == kModeForward)
+    x = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(o.x) + ((unsigned)w.packed & ~3u));
   StepEdges g;
   step_edges(r, w.s_in, v, w.a0, w.a1, w.a2, g);
-  const float3 D = g.D, e0 = g.e0, e1 = g.e1, e2 = g.e2;
-  // One bound from the longest edge settles all three signs in the common
-  // case; otherwise each edge gets its own bound before any float64 work.
+  // The exit face is opposite slot k when the signs of E(v, a_{k+1}) and
+  // E(v, a_{k+2}) are - and +; of three signs that are not all the same,
+  // exactly one pair is.
+  const unsigned long long n0 = __ballot(g.E0 < 0.f), n1 = __ballot(g.E1 < 0.f), n2 = __ballot(g.E2 < 0.f);
+  bool k0 = __builtin_amdgcn_inverse_ballot_w64(n1 & ~n2), k1 = __builtin_amdgcn_inverse_ballot_w64(n2 & ~n0),
+       k2 = __builtin_amdgcn_inverse_ballot_w64(n0 & ~n1);
   // (The branches that call out are marked as unlikely: the registers that a
   // call clobbers are then saved around it, not moved out of the whole loop.)
-  int k = step_exit_common(g);
-  if (__builtin_expect(k < 0, 0)) {
-    int s0 = step_edge_certified(g.E0, g.m0, g.K);
-    int s1 = step_edge_certified(g.E1, g.m1, g.K);
-    int s2 = step_edge_certified(g.E2, g.m2, g.K);
-    // One place that calls out, in a loop over the edges.
+  if (__builtin_expect(!(step_signs_certain(g, M.edge_max) & (k0 | k1 | k2)), 0)) {
+    int k = step_exit_common(g);
+    if (k < 0) {
+      // Each edge under its own bound, then in float64 or exactly.  One place
+      // that calls out, in a loop over the edges.
+      int s0 = step_edge_certified(g.E0, g.m0, g.K);
+      int s1 = step_edge_certified(g.E1, g.m1, g.K);
+      int s2 = step_edge_certified(g.E2, g.m2, g.K);
 #pragma unroll 1
-    for (int i = 0; i < 3; ++i) {
-      if ((i == 0 ? s0 : i == 1 ? s1 : s2) != 0) continue;
-      const float3 a = make_float3(i == 0 ? w.a0.x : i == 1 ? w.a1.x : w.a2.x,
-                                   i == 0 ? w.a0.y : i == 1 ? w.a1.y : w.a2.y,
-                                   i == 0 ? w.a0.z : i == 1 ? w.a1.z : w.a2.z);
-      const int sg = resolve_src(q, v, a, st);
-      s0 = i == 0 ? sg : s0;
-      s1 = i == 1 ? sg : s1;
-      s2 = i == 2 ? sg : s2;
+      for (int i = 0; i < 3; ++i) {
+        if ((i == 0 ? s0 : i == 1 ? s1 : s2) != 0) continue;
+        const float3 a = make_float3(i == 0 ? w.a0.x : i == 1 ? w.a1.x : w.a2.x,
+                                     i == 0 ? w.a0.y : i == 1 ? w.a1.y : w.a2.y,
+                                     i == 0 ? w.a0.z : i == 1 ? w.a1.z : w.a2.z);
+        const int sg = resolve_src(q, v, a, st);
+        s0 = i == 0 ? sg : s0;
+        s1 = i == 1 ? sg : s1;
+        s2 = i == 2 ? sg : s2;
+      }
+      k = exit_slot(s0, s1, s2);
     }
-    k = exit_slot(s0, s1, s2);
+    if (k == 3) {
+      st.add_failed();
+      st.take_back_step();
+      w.packed = -1;
+      return;
+    }
+    k0 = k == 0;
+    k1 = k == 1;
+    k2 = k == 2;
   }
-  if (__builtin_expect(k == 3, 0)) {
-    st.add_failed();
-    st.steps += w.steps;
-    return false;
-  }
-  w.steps++;
-  // Next tetrahedron across the exit face (local face index loc[k]): the
-  // record's load is issued as soon as the face is known, so that its
-  // latency overlaps the crossing and the segment's accumulation.
-  const int tet = w.tet;
-  const unsigned sh = (loc_table(MODE) ? 2u : 4u) * (unsigned)k;
-  unsigned f = (w.loc >> sh) & 3u;
-  float4 rec = M.faces[(size_t)(((unsigned)tet << 2) | f)];
-  const bool k0 = k == 0, k2 = k == 2;
-  const float3 ei = make_float3(k2 ? e0.x : (k0 ? e1.x : e2.x), k2 ? e0.y : (k0 ? e1.y : e2.y),
-                                k2 ? e0.z : (k0 ? e1.z : e2.z));
-  const float3 ej = make_float3(k2 ? e1.x : (k0 ? e2.x : e0.x), k2 ? e1.y : (k0 ? e2.y : e0.y),
-                                k2 ? e1.z : (k0 ? e2.z : e0.z));
-  float3 n = f3cross(ei, ej);
-  float den = f3dot(r.d, n);
+  // Next tetrahedron across the exit face (its local index is in slot k's
+  // field of loc): the record's load is issued as soon as the face is known,
+  // so that its latency overlaps the crossing and the segment's accumulation.
+  const unsigned L = w.loc, sh = k0 ? 0u : k1 ? 2u : 4u;
+  const unsigned at = ((unsigned)w.packed & ~3u) | ((L >> sh) & 3u);
+  float4 rec = M.faces[(size_t)at];
+  // The exit face is the next entry face: slot k takes v.
+  w.a0 = make_float3(k0 ? v.x : w.a0.x, k0 ? v.y : w.a0.y, k0 ? v.z : w.a0.z);
+  w.a1 = make_float3(k1 ? v.x : w.a1.x, k1 ? v.y : w.a1.y, k1 ? v.z : w.a1.z);
+  w.a2 = make_float3(k2 ? v.x : w.a2.x, k2 ? v.y : w.a2.y, k2 ? v.z : w.a2.z);
+  const float3 n = f3cross(f3sub(w.a1, w.a0), f3sub(w.a2, w.a0));
+  const float den = f3dot(r.d, n);
   float dt;
   if (__builtin_expect(fabsf(den) > r.gd * fmaxf(fabsf(n.x), fmaxf(fabsf(n.y), fabsf(n.z))), 1)) {
-    dt = f3dot(D, n) * __builtin_amdgcn_rcpf(den);  // v_rcp_f32, about 1 ulp
+    dt = f3dot(g.D, n) * __builtin_amdgcn_rcpf(den);  // (v is on the face); v_rcp_f32, about 1 ulp
   } else {
     st.add_grazing();
-    const float3 ai = make_float3(k2 ? w.a0.x : (k0 ? w.a1.x : w.a2.x), k2 ? w.a0.y : (k0 ? w.a1.y : w.a2.y),
-                                  k2 ? w.a0.z : (k0 ? w.a1.z : w.a2.z));
-    const float3 aj = make_float3(k2 ? w.a1.x : (k0 ? w.a2.x : w.a0.x), k2 ? w.a1.y : (k0 ? w.a2.y : w.a0.y),
-                                  k2 ? w.a1.z : (k0 ? w.a2.z : w.a0.z));
-    dt = (float)(crossing_s_fp64(q.S(), q.P(), v, ai, aj) - w.s_in);
+    dt = (float)(crossing_s_fp64(q.S(), q.P(), w.a0, w.a1, w.a2) - w.s_in);
   }
-  if (w.far)  // (1, the whole ray's parameter range, is an inline constant)
+  if (__builtin_expect(w.far, 1))  // (1, the whole ray's parameter range, is an inline constant)
     dt = __builtin_amdgcn_fmed3f(dt, 0.0f, 1.0f);
   else
     dt = __builtin_amdgcn_fmed3f(dt, 0.0f, (float)fmax(0.5 - w.s_in, 0.0));
-  if (dt == 0.f) st.add_zero();
+  if (__builtin_expect(dt == 0.f, 0)) st.add_zero();
   if constexpr (MODE == kModeForward) {
-    o.acc = fma((double)dt, (double)w.xcur, o.acc);  // the product is exact
-  } else if constexpr (MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeBackExact) {
+    o.acc = fma((double)dt, (double)x, o.acc);  // the product is exact
+  } else if constexpr (kTable) {
     // Every segment goes into the table, a zero-length one as 0 (dt is never
     // negative or NaN after the clamp): adding zero costs less than a branch
     // per step, and the step's claim is then consumed on every path.
-    const float v = dt * o.weight;  // in units of 2^-scale_exp
-    const long long m = round_to_i64(v);
-    if (!lds_accumulate<kScatterSlots>(o.lds_keys, o.lds_vals, tet, m,
-                                                 w.home, w.claim)) {
+    const float t = dt * o.weight;  // in units of 2^-scale_exp
+    const long long m = round_to_i64(t);
+    if (!lds_accumulate<kScatterSlots>(o.lds_keys, o.lds_vals, tet, m, w.home, w.claim)) {
       if constexpr (MODE == kModeBackFixed) {
         atomicAdd(o.acc64 + tet, (unsigned long long)m);
       } else if constexpr (MODE == kModeBackExact) {
         add_exact(o.exact, M.nt, tet, o.scale_exp, m);
       } else {
-        unsafeAtomicAdd(o.xhat + tet, ldexpf(v, -o.scale_exp));
+        unsafeAtomicAdd(o.xhat + tet, ldexpf(t, -o.scale_exp));
       }
     }
   } else if constexpr (MODE == kModeBackDirect) {
@@ -614,100 +609,86 @@ __device__ __forceinline__ bool walk_step(const MeshView& M, const Ray& r, const
     o.out_len[o.cursor] = dt * r.dn;
     o.cursor++;
   }
-  // What does not need the record is done while it is in flight: the entry
-  // slots (slot k takes v), the ray parameter, and the first half of the
-  // local-index remap: the table row (loc, k), or, bit-parallel, all four
-  // index fields at once: adding 7 - f to a field sets its bit 3 exactly
-  // when p > f, and adding 8 - back to the rank sets it exactly when r >=
-  // back; the fields hold at most 10, so no carry crosses into the next.
-  // (The field of slot k, whose vertex is not on the face, is replaced.)
-  const unsigned L = w.loc;
-  const unsigned R = loc_table(MODE) ? (L * 3u + (unsigned)k) * 4u
-                                     : L - (((L + 0x7777u - f * 0x1111u) >> 3) & 0x1111u);
-  w.a0 = make_float3(k == 0 ? v.x : w.a0.x, k == 0 ? v.y : w.a0.y, k == 0 ? v.z : w.a0.z);
-  w.a1 = make_float3(k == 1 ? v.x : w.a1.x, k == 1 ? v.y : w.a1.y, k == 1 ? v.z : w.a1.z);
-  w.a2 = make_float3(k == 2 ? v.x : w.a2.x, k == 2 ? v.y : w.a2.y, k == 2 ? v.z : w.a2.z);
   w.s_in += (double)dt;  // float64: no rounding drift along the ray
-  unsigned Rk = R;
-  // (An empty statement that takes these values, so the compiler computes
-  // them here rather than sinking them behind the wait for the record.)
+  unsigned R = __umul24(L, 12u) + sh * 2u;  // the remap's row (loc, k)
+  // What does not need the record is done while it is in flight.  (An empty
+  // statement that takes these values, so the compiler computes them here
+  // rather than sinking them behind the wait for the record.)
   asm volatile("" : "+v"(w.a0.x), "+v"(w.a0.y), "+v"(w.a0.z), "+v"(w.a1.x), "+v"(w.a1.y), "+v"(w.a1.z),
-               "+v"(w.a2.x), "+v"(w.a2.y), "+v"(w.a2.z), "+v"(w.s_in), "+v"(Rk));
+               "+v"(w.a2.x), "+v"(w.a2.y), "+v"(w.a2.z), "+v"(w.s_in), "+v"(R));
   // Keep the record one 16-byte load consumed here; otherwise the compiler
   // splits it into four loads sunk into the next step, which serialises the
   // dependent fetch behind the next step's arithmetic.
   asm volatile("" : "+v"(rec.x), "+v"(rec.y), "+v"(rec.z), "+v"(rec.w));
-  int packed = __float_as_int(rec.x);
-  if (packed < 0) {
-    st.steps += w.steps;
-    return false;
-  }
-  unsigned back = (unsigned)packed & 3u;
-  if constexpr (loc_table(MODE)) {
-    // Read back while the next step computes; needed at its exit face.
-    w.loc = s_loc_remap[Rk + back];
-  } else {
-    const unsigned N = Rk + (((Rk + 0x8888u - back * 0x1111u) >> 3) & 0x1111u);
-    // Slot k takes v's new index; the neighbour's opposite vertex is `back`.
-    const unsigned fieldk = 0xFu << sh;
-    w.loc = (((N & 0xFFFu) & ~fieldk) | ((N >> 12) << sh)) | (back << 12);
-  }
+  w.packed = __float_as_int(rec.x);
   w.v = xyz(rec);
-  w.tet = packed >> 2;
+  if (w.packed < 0) return;
+  // Read back while the next step computes; needed at its exit face.
+  w.loc = s_loc_remap[R + ((unsigned)w.packed & 3u)];
   // Table walks claim the new tetrahedron's home slot now; the old key comes
   // back while the next step computes, and is needed only at its end.
-  if constexpr (MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeBackExact) {
-    w.home = table_home<kScatterSlots>(w.tet);
-    w.claim = lds_cas(o.lds_keys + w.home, w.tet);
+  if constexpr (kTable) {
+    w.home = table_home<kScatterSlots>(w.packed >> 2);
+    w.claim = lds_cas(o.lds_keys + w.home, w.packed >> 2);
   }
-  if constexpr (MODE == kModeForward) w.xcur = o.x[w.tet];
-  return true;
 }
 
-// Walk one ray from boundary face `entry` to the boundary.
+// Takes up to `limit` steps with the wavefront's live rays together and
+// returns how many they took in all.  Every lane calls it.
 template <int MODE, class Src, class St>
-__device__ __forceinline__ void walk_ray(const MeshView& M, const Ray& r, const Src& q, int entry, WalkOut<MODE>& o,
-                                         St& st) {
-  WalkState w;
-  // Called by the lanes that walk: the vote is over them.
-  walk_start<MODE>(M, r, q, entry, w, o, __all(ends_beyond_mesh(r, M.extent)) != 0);
-  while (walk_step<MODE>(M, r, q, w, o, st)) {
+__device__ __forceinline__ int walk_steps(const MeshView& M, const Ray& r, const Src& q, WalkState& w,
+                                          WalkOut<MODE>& o, St& st, int limit) {
+  int segments = 0;
+#pragma unroll 1
+  for (int k = 0; k < limit; ++k) {
+    const unsigned long long live = __ballot(w.packed >= 0);
+    if (!live) break;
+    segments += __popcll(live);
+    if (w.packed >= 0) walk_step<MODE>(M, r, q, w, o, st);
   }
+  return segments;
+}
+
+// Walks the wavefront's rays, those of the lanes with `alive`, from their
+// boundary faces to the boundary; returns the steps they took.
+template <int MODE, class Src, class St>
+__device__ __forceinline__ int walk_rays(const MeshView& M, const Ray& r, const Src& q, int entry, WalkOut<MODE>& o,
+                                         St& st, bool alive) {
+  WalkState w{};
+  w.packed = -1;
+  const bool far = __ballot(alive && !ends_beyond_mesh(r, M.extent)) == 0;
+  if (alive) walk_start<MODE>(M, r, q, entry, w, o, far);
+  w.far = far;
+  const int segments = walk_steps<MODE>(M, r, q, w, o, st, M.nt + 1);
+  if (w.packed >= 0) st.add_failed();
+  return segments;
 }
 
 // Adds a wavefront's counts to the mesh's counters with one atomic
 // instruction, a lane per counter: shuffle reductions of the lane registers
-// (of the rare events' only when the wavefront had any), or (LdsStats) every
-// lane's ray and step counts added to the wavefront's LDS counters.
-__device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
-
-__device__ __forceinline__ void flush_stats(const MeshView& M, RegStats& st, int active) {
+// when the wavefront had any event (RegStats), or the LDS counters.
+__device__ __forceinline__ void flush_stats(const MeshView& M, RegStats& st, int rays) {
   const int lane = threadIdx.x & 63;
-  const int rays = __popcll(__ballot(active)), steps = wave_sum(st.steps);
-  int v = lane == kRays ? rays : lane == kSegments ? steps : 0;
+  int v = lane == kRays ? rays : 0;
   if (__ballot(st.zero | st.fp64 | st.exact | st.pert | st.failed | st.grazing)) {
     const int rare[6] = {st.zero, st.fp64, st.exact, st.pert, st.failed, st.grazing};
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
-      const int x = wave_sum(rare[c]);
+      int x = rare[c];
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
       if (lane == kZeroLen + c) v = x;
     }
   }
   if (v) atomicAdd(counter_row(M) + lane, (unsigned long long)v);
 }
 
-__device__ __forceinline__ void flush_stats(const MeshView& M, LdsStats& st, int active) {
-  if (active) lds_add_u32(st.ev + kEvRays, 1u);
-  if (st.steps) lds_add_u32(st.ev + kEvSteps, (unsigned)st.steps);
+__device__ __forceinline__ void flush_stats(const MeshView& M, LdsStats& st, int rays, int segments) {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
   const int lane = threadIdx.x & 63;
   if (lane < kEvents) {
-    const unsigned v = st.ev[lane];
+    const unsigned v = st.ev[lane] + (unsigned)(lane == kEvRays ? rays : lane == kEvSteps ? segments : 0);
     const int slot = lane == kEvRays ? kRays : lane == kEvSteps ? kSegments : kZeroLen + lane;
     if (v) atomicAdd(counter_row(M) + slot, (unsigned long long)v);
   }
@@ -772,11 +753,13 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
                                            long long* tvals) {
   int a, i, j;
   bool active = tile_ray(G, tm, block, threadIdx.x, a0, na_chunk, &a, &i, &j);
-  // The scatter walks keep their rare counts in LDS, the others in registers.
   constexpr bool kTable = MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeBackExact;
-  using St = typename std::conditional<kTable, LdsStats, RegStats>::type;
-  __shared__ unsigned s_ev[kTable ? kBlockWaves * kEvents : 1];
-  St st(kTable ? wave_counters(s_ev) : nullptr);
+  constexpr bool kEntryOnly = MODE == kModeEntry || MODE == kModeEntryRstar;
+  using St = typename std::conditional<kEntryOnly, RegStats, LdsStats>::type;
+  __shared__ unsigned s_ev[kEntryOnly ? 1 : kBlockWaves * kEvents];
+  St st(kEntryOnly ? nullptr : wave_counters(s_ev));
+  const int rays = __popcll(__ballot(active));
+  int segments = 0;
   if constexpr (kTable) {
     const int lane = threadIdx.x & 63;
     constexpr int kSlots = kScatterSlots, kWindow = kScatterWindow;
@@ -792,8 +775,8 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
     o.xhat = io.out_f32;
     o.lds_keys = keys;
     o.lds_vals = vals;
-    WalkState w;
-    bool alive = false;
+    WalkState w{};
+    w.packed = -1;
     bool ends_far = true;
     if (active) {
       int64_t rid = ((int64_t)a * G.nv + j) * G.nu + i;
@@ -806,10 +789,7 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
       else
         e = io.entry ? io.entry[rid] : find_entry(M, r, st);
       o.weight = io.in[rid] * r.dn;
-      if (e >= 0 && o.weight != 0.f) {
-        walk_start<MODE>(M, r, q, e, w, o, false);
-        alive = true;
-      }
+      if (e >= 0 && o.weight != 0.f) walk_start<MODE>(M, r, q, e, w, o, false);
     }
     w.far = __all(ends_far) != 0;
     if constexpr (MODE == kModeBackFixed) {
@@ -827,7 +807,7 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
       if (lane == 0) *wm = 0u;
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      if (alive)
+      if (w.packed >= 0)
         __hip_atomic_fetch_max(wm, __float_as_uint(fabsf(o.weight)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
@@ -837,27 +817,24 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
       o.lds_scale = ldexpf(1.0f, o.scale_exp);
     }
     o.weight *= o.lds_scale;  // a power of two: exact
-    // The wavefront's rays start together and every live one takes one step
-    // per iteration, so all of them have taken `taken` steps at a window's
-    // start: the step bound is checked there, once per window.
-    int taken = 0;
     // The wavefront's rays advance together in windows of kWindow
     // steps; after each window its table is added to xhat and cleared, so it
-    // only ever holds the tetrahedra of one window of the ray bundle.
+    // only ever holds the tetrahedra of one window of the ray bundle.  (All
+    // live rays have taken the same number of steps, `taken` at a window's
+    // start, where the step bound is checked.)
+    int taken = 0;
     for (;;) {
       // Each step claims the slot of the tetrahedron it enters (walk_step);
       // the flush has cleared the table, so the current ones claim again.
-      if (alive) {
-        w.home = table_home<kSlots>(w.tet);
-        w.claim = lds_cas(keys + w.home, w.tet);
+      if (w.packed >= 0) {
+        w.home = table_home<kSlots>(w.packed >> 2);
+        w.claim = lds_cas(keys + w.home, w.packed >> 2);
       }
-      if (taken > M.nt && alive) {
+      if (taken > M.nt && w.packed >= 0) {
         st.add_failed();
-        st.steps += w.steps;
-        alive = false;
+        w.packed = -1;
       }
-#pragma unroll 1
-      for (int k = 0; k < kWindow && alive; ++k) alive = walk_step<MODE, false>(M, r, q, w, o, st);
+      segments += walk_steps<MODE>(M, r, q, w, o, st, kWindow);
       taken += kWindow;
       // LDS operations of one wavefront complete in order: the flush sees
       // every add of the window.
@@ -881,42 +858,47 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      if (__ballot(alive) == 0) break;
+      if (__ballot(w.packed >= 0) == 0) break;
     }
-  } else if (active) {
-    int64_t rid = ((int64_t)a * G.nv + j) * G.nu + i;
-    Ray r = cone_ray(G, M.extent, a, i, j);
+    flush_stats(M, st, rays, segments);
+  } else if constexpr (kEntryOnly) {
+    if (active) {
+      const Ray r = cone_ray(G, M.extent, a, i, j);
+      io.out_i32[((int64_t)a * G.nv + j) * G.nu + i] = find_entry<MODE == kModeEntryRstar>(M, r, st);
+    }
+    flush_stats(M, st, rays);
+  } else {
+    const int64_t rid = ((int64_t)a * G.nv + j) * G.nu + i;
     // The single-problem walks have registers to spare, so their exact paths
     // read the ray from registers; the batched ones (and the windowed
     // backprojection) re-read it from the frame.
     using Src = typename std::conditional<kLeanSrc, PixelSrc, RegSrc>::type;
-    Src q;
-    if constexpr (kLeanSrc)
-      q = pixel_src(G, a, i, j);
-    else
-      q = RegSrc{r.S, r.P, r.U, r.V};
-    int e;
-    if constexpr (MODE == kModeEntryRstar)
-      e = find_entry<true>(M, r, st);
-    else if constexpr (kCached && MODE != kModeEntry)
-      e = io.entry[rid];
-    else
-      e = (io.entry && MODE != kModeEntry) ? io.entry[rid] : find_entry(M, r, st);
-    if constexpr (MODE == kModeEntry || MODE == kModeEntryRstar) {
-      io.out_i32[rid] = e;
-    } else if constexpr (MODE == kModeForward) {
-      WalkOut<MODE> o;
-      o.x = io.in;
-      if (e >= 0) walk_ray<MODE>(M, r, q, e, o, st);
-      io.out_f32[rid] = (float)(o.acc * (double)r.dn);
-    } else if constexpr (MODE == kModeBackDirect) {
-      WalkOut<MODE> o;
-      o.xhat = io.out_f32;
-      o.weight = io.in[rid] * r.dn;
-      if (e >= 0 && o.weight != 0.f) walk_ray<MODE>(M, r, q, e, o, st);
+    Ray r{};
+    Src q{};
+    WalkOut<MODE> o;
+    int e = -1;
+    if (active) {
+      r = cone_ray(G, M.extent, a, i, j);
+      if constexpr (kLeanSrc)
+        q = pixel_src(G, a, i, j);
+      else
+        q = RegSrc{r.S, r.P, r.U, r.V};
+      if constexpr (kCached)
+        e = io.entry[rid];
+      else
+        e = io.entry ? io.entry[rid] : find_entry(M, r, st);
     }
+    if constexpr (MODE == kModeForward) {
+      o.x = io.in;
+      segments = walk_rays<MODE>(M, r, q, e, o, st, e >= 0);
+      if (active) io.out_f32[rid] = (float)(o.acc * (double)r.dn);
+    } else {
+      o.xhat = io.out_f32;
+      if (active) o.weight = io.in[rid] * r.dn;
+      segments = walk_rays<MODE>(M, r, q, e, o, st, e >= 0 && o.weight != 0.f);
+    }
+    flush_stats(M, st, rays, segments);
   }
-  flush_stats(M, st, active ? 1 : 0);
 }
 
 }  // namespace
@@ -926,7 +908,7 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
 template <int MODE, bool kCached>
 __global__ __launch_bounds__(256, 4) void pixel_walk_kernel(MeshView M, GeomView G, TileMap tm, int a0, int na_chunk,
                                                          BlockIO io) {
-  if constexpr (loc_table(MODE)) load_loc_remap();
+  if constexpr (MODE != kModeEntry && MODE != kModeEntryRstar) load_loc_remap();
   if constexpr (MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeBackExact) {
     __shared__ int tkeys[kBlockWaves * kScatterSlots];
     __shared__ long long tvals[kBlockWaves * kScatterSlots];
@@ -1104,7 +1086,7 @@ __global__ __launch_bounds__(256, 4) void batch_walk_kernel(const BatchDesc* __r
   // Thread 0 fetches `chunk` positions at a time and resolves each to a
   // (problem, pixel block) for the whole block; its state lives in LDS so
   // that nothing of the queue stays live in registers during the walk.
-  if constexpr (loc_table(MODE)) load_loc_remap();
+  load_loc_remap();
   __shared__ long long s_k, s_end, s_block;
   __shared__ int s_list, s_prob;
   const int home = (int)(blockIdx.x % kXcds);
@@ -1198,11 +1180,16 @@ __global__ __launch_bounds__(256) void list_walk_kernel(MeshView M, GeomView G, 
                                                         const float* P, const float* U, const float* V, int32_t n,
                                                         int64_t* counts, const int64_t* offsets, int32_t* tets,
                                                         float* lens) {
-  int k = blockIdx.x * blockDim.x + threadIdx.x;
-  RegStats st(nullptr);
-  bool active = k < n;
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  load_loc_remap();
+  __shared__ unsigned s_ev[kBlockWaves * kEvents];
+  LdsStats st(wave_counters(s_ev));
+  const bool active = k < n;
+  Ray r{};
+  RegSrc q{};
+  WalkOut<MODE> o;
+  int e = -1;
   if (active) {
-    Ray r;
     if (ids) {
       int64_t rid = ids[k];
       int i = (int)(rid % G.nu);
@@ -1219,21 +1206,22 @@ __global__ __launch_bounds__(256) void list_walk_kernel(MeshView M, GeomView G, 
     // {P - S, U, V} must be a basis for the tie-breaking translation.
     float s3[3] = {r.S.x, r.S.y, r.S.z}, p3[3] = {r.P.x, r.P.y, r.P.z}, u3[3] = {r.U.x, r.U.y, r.U.z},
           v3[3] = {r.V.x, r.V.y, r.V.z};
-    bool basis = det_diff_sign(p3, s3, u3, nullptr, v3, nullptr, nullptr) != 0;
-    int e = basis ? find_entry(M, r, st) : -1;
-    if (!basis) st.add_failed();
-    const RegSrc q{r.S, r.P, r.U, r.V};
-    WalkOut<MODE> o;
+    if (det_diff_sign(p3, s3, u3, nullptr, v3, nullptr, nullptr) != 0)
+      e = find_entry(M, r, st);
+    else
+      st.add_failed();
+    q = RegSrc{r.S, r.P, r.U, r.V};
     if constexpr (MODE == kModeTrace) {
       o.out_tet = tets;
       o.out_len = lens;
       o.perm = M.perm;
       o.cursor = offsets[k];
     }
-    if (e >= 0) walk_ray<MODE>(M, r, q, e, o, st);
-    if constexpr (MODE == kModeCountAll) counts[k] = o.count;
   }
-  flush_stats(M, st, active ? 1 : 0);
+  const int segments = walk_rays<MODE>(M, r, q, e, o, st, e >= 0);
+  if constexpr (MODE == kModeCountAll)
+    if (active) counts[k] = o.count;
+  flush_stats(M, st, __popcll(__ballot(active)), segments);
 }
 
 // Reproducible scatter: clears the integer sums and the largest |y_j|, finds

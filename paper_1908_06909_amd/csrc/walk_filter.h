@@ -173,8 +173,15 @@ __host__ __device__ __forceinline__ void step_edges(const Ray& r, double s, floa
   g.m2 = fmaxf(fabsf(g.e2.x), fmaxf(fabsf(g.e2.y), fabsf(g.e2.z)));
 }
 
-// One bound from the longest edge settles all three signs in the common
-// case: returns the exit slot (0..2; 3 when all three signs agree, a failed
+// The same bound from the longest edge of the whole mesh (the largest |e|_inf
+// of any edge, as rounded in float32): all three signs are those of E0, E1 and
+// E2 when this holds.  It spares the step the magnitudes of its own edges; a
+// mesh with elements of very different sizes comes back to them more often.
+__host__ __device__ __forceinline__ bool step_signs_certain(const StepEdges& g, float edge_max) {
+  return fminf(fabsf(g.E0), fminf(fabsf(g.E1), fabsf(g.E2))) > fmaf(edge_max, g.K, kFilterAbs);
+}
+
+// One bound from the step's longest edge: returns the exit slot (0..2; 3 when all three signs agree, a failed
 // walk), or -1 when some sign is uncertain under that bound.
 __host__ __device__ __forceinline__ int step_exit_common(const StepEdges& g) {
   if (fminf(fabsf(g.E0), fminf(fabsf(g.E1), fabsf(g.E2))) > fmaf(fmaxf(g.m0, fmaxf(g.m1, g.m2)), g.K, kFilterAbs)) {
