@@ -480,10 +480,14 @@ __global__ __launch_bounds__(kShadowThreads) void shadow_exact_kernel(ShadowArgs
   const int nt = A.M.nt;
   const int count = *A.dirty_count;
   ShadowStats st;
-  // One wavefront per deferred item; lane l takes the angles a_begin + l,
-  // a_begin + l + 64, ... in order, and the 64 partial sums are combined in
-  // a fixed butterfly order (lane 0's result is stored), so the sum is the
-  // same on every run.
+  // One wavefront per deferred item.  Lane l takes the angles a_begin + l,
+  // a_begin + l + 64, ... in order, or of every angle the shadow's pixels l,
+  // l + 64, ..., whichever leaves fewer turns (an angle's projection costs
+  // about 2.5 pixels); the 64 partial sums are combined in a fixed butterfly
+  // order (lane 0's result is stored), so the sum is the same on every run.
+  // Few elements have large shadows and chunks of few angles: with the angles
+  // alone, 2 of 64 lanes worked, and 8^3 500x400x150 took 11.5 ms, 7.2 with
+  // the pixels.
   const int lane = threadIdx.x & 63;
   const int wave = (blockIdx.x * kShadowThreads + threadIdx.x) >> 6;
   const int nwaves = (gridDim.x * kShadowThreads) >> 6;
@@ -496,9 +500,21 @@ __global__ __launch_bounds__(kShadowThreads) void shadow_exact_kernel(ShadowArgs
     float3 v[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) v[q] = tet_vertex(tq, q);
+    bool by_pixel = false;
+    {
+      const FrameD F = load_frame(A.G.frame, a_begin);
+      double al[4], be[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) project_vertex(F, v[q], al[q], be[q]);
+      int i0, i1, j0, j1;
+      if (shadow_box(A, al, be, i0, i1, j0, j1)) {
+        const int64_t n = (int64_t)(i1 - i0 + 1) * (j1 - j0 + 1), na = a_end - a_begin;
+        by_pixel = na * (5 + 2 * ((n + 63) / 64)) < (na + 63) / 64 * (5 + 2 * n);
+      }
+    }
     double acc = 0.0;
 #pragma unroll 1
-    for (int a = a_begin + lane; a < a_end; a += 64) {
+    for (int a = a_begin + (by_pixel ? 0 : lane); a < a_end; a += by_pixel ? 1 : 64) {
       FrameD F = load_frame(A.G.frame, a);
       double al[4], be[4];
 #pragma unroll
@@ -506,69 +522,69 @@ __global__ __launch_bounds__(kShadowThreads) void shadow_exact_kernel(ShadowArgs
       int i0, i1, j0, j1;
       if (!shadow_box(A, al, be, i0, i1, j0, j1)) continue;
       const float* yrow = A.proj + (size_t)a * nv * nu;
+      // The box's pixels in row order, from `first` in steps of `step`.
+      const int w = i1 - i0 + 1, first = by_pixel ? lane : 0, step = by_pixel ? 64 : 1;
+      const int di = step % w, dj = step / w;
+      int i = i0 + first % w, j = j0 + first / w;
 #pragma unroll 1
-      for (int j = j0; j <= j1; ++j) {
-        const float vv = vt[j];
-#pragma unroll 1
-        for (int i = i0; i <= i1; ++i) {
-          const float3 P = pixel_point(F.f, ut[i], vv);
-          const double dx = (double)P.x - F.Sx, dy = (double)P.y - F.Sy, dz = (double)P.z - F.Sz;
-          const float3 df = f3sub(P, F.S);
-          const float dinf = fmaxf(fabsf(df.x), fmaxf(fabsf(df.y), fabsf(df.z)));
-          float E[6];
-          int pos = 0, neg = 0;
+      for (; j <= j1; i += di, j += dj, j += i > i1 ? 1 : 0, i -= i > i1 ? w : 0) {
+        const float3 P = pixel_point(F.f, ut[i], vt[j]);
+        const double dx = (double)P.x - F.Sx, dy = (double)P.y - F.Sy, dz = (double)P.z - F.Sz;
+        const float3 df = f3sub(P, F.S);
+        const float dinf = fmaxf(fabsf(df.x), fmaxf(fabsf(df.y), fabsf(df.z)));
+        float E[6];
+        int pos = 0, neg = 0;
 #pragma unroll
-          for (int e = 0; e < 6; ++e) {
-            const int pe = e < 3 ? 0 : (e < 5 ? 1 : 2);
-            const int qe = e < 3 ? e + 1 : (e < 5 ? e - 1 : 3);
-            double Ed;
-            int s = edge_sign_fp64(F, dx, dy, dz, dinf, v[pe], v[qe], &Ed);
-            E[e] = (float)Ed;
-            pos |= (s > 0) << e;
-            neg |= (s < 0) << e;
-          }
-          int unk = 0x3f & ~(pos | neg);
-          while (unk) {
-            // One call site; the two vertices re-read from memory.
-            const int e = __ffs(unk) - 1;
-            unk &= unk - 1;
-            const int pe = (0x211000 >> (4 * e)) & 3, qe = (0x332321 >> (4 * e)) & 3;
-            const int res = slow_edge_sign(F.S, P, F.U, F.V, tet_vertex(tq, pe), tet_vertex(tq, qe));
-            const int s = (res & 3) - 1;
-            st.slow++;
-            if (res & (kFlagExact << 2)) st.exact++;
-            if (res & (kFlagPerturbed << 2)) st.pert++;
-            pos |= (s > 0) << e;
-            neg |= (s < 0) << e;
-          }
-          const int fe = entry_face(neg, pos);
-          if (fe < 0) continue;
-          const int fx = entry_face(pos, neg);
-          if (fx < 0) continue;
-          st.hits++;
-          // Crossing points from the edge values: for face (a, b, c) the
-          // weight of a is E(b, c).  With lambda_k = (v_k - v0) . d the
-          // chord is (sum_k w^x_k lambda_k / W_x - sum_k w^e_k lambda_k / W_e) / |d|.
-          const float3 d = df;
-          const float l1 = f3dot(f3sub(v[1], v[0]), d), l2 = f3dot(f3sub(v[2], v[0]), d),
-                      l3 = f3dot(f3sub(v[3], v[0]), d);
-          float Nf[4], Wf[4];
-          Nf[0] = E[5] * l1 - E[4] * l2 + E[3] * l3;
-          Wf[0] = E[5] - E[4] + E[3];
-          Nf[1] = E[2] * l2 - E[1] * l3;
-          Wf[1] = E[2] - E[5] - E[1];
-          Nf[2] = E[0] * l3 - E[2] * l1;
-          Wf[2] = E[4] - E[2] + E[0];
-          Nf[3] = E[1] * l1 - E[0] * l2;
-          Wf[3] = E[1] - E[3] - E[0];
-          const float ne = fe == 0 ? Nf[0] : fe == 1 ? Nf[1] : fe == 2 ? Nf[2] : Nf[3];
-          const float we = fe == 0 ? Wf[0] : fe == 1 ? Wf[1] : fe == 2 ? Wf[2] : Wf[3];
-          const float nx = fx == 0 ? Nf[0] : fx == 1 ? Nf[1] : fx == 2 ? Nf[2] : Nf[3];
-          const float wx = fx == 0 ? Wf[0] : fx == 1 ? Wf[1] : fx == 2 ? Wf[2] : Wf[3];
-          float L = (nx / wx - ne / we) * __frsqrt_rn(f3dot(d, d));
-          L = fmaxf(L, 0.f);
-          acc = fma((double)L, (double)yrow[(size_t)j * nu + i], acc);
+        for (int e = 0; e < 6; ++e) {
+          const int pe = e < 3 ? 0 : (e < 5 ? 1 : 2);
+          const int qe = e < 3 ? e + 1 : (e < 5 ? e - 1 : 3);
+          double Ed;
+          int s = edge_sign_fp64(F, dx, dy, dz, dinf, v[pe], v[qe], &Ed);
+          E[e] = (float)Ed;
+          pos |= (s > 0) << e;
+          neg |= (s < 0) << e;
         }
+        int unk = 0x3f & ~(pos | neg);
+        while (unk) {
+          // One call site; the two vertices re-read from memory.
+          const int e = __ffs(unk) - 1;
+          unk &= unk - 1;
+          const int pe = (0x211000 >> (4 * e)) & 3, qe = (0x332321 >> (4 * e)) & 3;
+          const int res = slow_edge_sign(F.S, P, F.U, F.V, tet_vertex(tq, pe), tet_vertex(tq, qe));
+          const int s = (res & 3) - 1;
+          st.slow++;
+          if (res & (kFlagExact << 2)) st.exact++;
+          if (res & (kFlagPerturbed << 2)) st.pert++;
+          pos |= (s > 0) << e;
+          neg |= (s < 0) << e;
+        }
+        const int fe = entry_face(neg, pos);
+        if (fe < 0) continue;
+        const int fx = entry_face(pos, neg);
+        if (fx < 0) continue;
+        st.hits++;
+        // Crossing points from the edge values: for face (a, b, c) the
+        // weight of a is E(b, c).  With lambda_k = (v_k - v0) . d the
+        // chord is (sum_k w^x_k lambda_k / W_x - sum_k w^e_k lambda_k / W_e) / |d|.
+        const float3 d = df;
+        const float l1 = f3dot(f3sub(v[1], v[0]), d), l2 = f3dot(f3sub(v[2], v[0]), d),
+                    l3 = f3dot(f3sub(v[3], v[0]), d);
+        float Nf[4], Wf[4];
+        Nf[0] = E[5] * l1 - E[4] * l2 + E[3] * l3;
+        Wf[0] = E[5] - E[4] + E[3];
+        Nf[1] = E[2] * l2 - E[1] * l3;
+        Wf[1] = E[2] - E[5] - E[1];
+        Nf[2] = E[0] * l3 - E[2] * l1;
+        Wf[2] = E[4] - E[2] + E[0];
+        Nf[3] = E[1] * l1 - E[0] * l2;
+        Wf[3] = E[1] - E[3] - E[0];
+        const float ne = fe == 0 ? Nf[0] : fe == 1 ? Nf[1] : fe == 2 ? Nf[2] : Nf[3];
+        const float we = fe == 0 ? Wf[0] : fe == 1 ? Wf[1] : fe == 2 ? Wf[2] : Wf[3];
+        const float nx = fx == 0 ? Nf[0] : fx == 1 ? Nf[1] : fx == 2 ? Nf[2] : Nf[3];
+        const float wx = fx == 0 ? Wf[0] : fx == 1 ? Wf[1] : fx == 2 ? Wf[2] : Wf[3];
+        float L = (nx / wx - ne / we) * __frsqrt_rn(f3dot(d, d));
+        L = fmaxf(L, 0.f);
+        acc = fma((double)L, (double)yrow[(size_t)j * nu + i], acc);
       }
     }
 #pragma unroll
