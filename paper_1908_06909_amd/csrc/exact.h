@@ -17,14 +17,17 @@
 // largest component.
 //
 // Nearly all determinants that get here have columns whose entries, scaled by
-// a power of two of the column's own, are integers below 2^41 (mesh and
-// detector coordinates of similar size).  Those are decided in 128-bit integer
-// arithmetic: some 500 instructions in registers, against several thousand
-// dependent ones on an array in scratch memory for the expansion, which one
-// ray through an edge makes its whole wavefront wait for, several times in a
-// row: a walk of 65,536 rays through 3,072 tetrahedra, 1,077 signs of it
-// ties, takes 0.10 ms with the integers and 0.37 with the expansion; one of
-// 2.9M rays with 3.1M ties 5.1 ms and 8.1.
+// a power of two of the column's own, are integers below 2^42 (mesh and
+// detector coordinates of similar size).  Those are decided in integer
+// arithmetic: some 400 instructions in registers, against several thousand
+// dependent ones on an array in scratch memory for the expansion.  What bounds
+// a small launch is the latency of these signs, which one ray through an edge
+// makes its whole wavefront wait for, some 30 times in a row along a diagonal
+// of a regular mesh: a walk of 65,536 rays through 3,072 tetrahedra takes
+// 0.03 ms without a tie and, with 1,082, 0.37 ms with the expansion, 0.09 with
+// 128-bit integers in a function of their own, and 0.07 with 30-bit digits
+// inline in the walk, whose registers then need not be saved around a call;
+// one of 2.9M rays with 3.1M ties 8.1, 5.0 and 4.0 ms.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -106,55 +109,64 @@ __host__ __device__ __attribute__((noinline)) inline int expansion_det_diff_sign
   return e[n - 1] > 0.0 ? 1 : -1;
 }
 
-// The column a1 - a0 times a power of two as integers, |c| <= 2^41; false when
-// a scaled coordinate is not an integer below 2^51.  (The scale puts the
-// largest difference, rounded, into [2^40, 2^41); a0 = null is zero.)
+// The column a1 - a0 times a power of two as integers, |c| < 2^42; false when
+// a scaled coordinate is not an integer.  (The scale puts the largest
+// coordinate into [2^40, 2^41); a0 = null is zero.)
 __host__ __device__ inline bool column_to_int(const float* a1, const float* a0, long long* c) {
-  double x1[3], x0[3];
   double m = 0.0;
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    x1[i] = (double)a1[i];
-    x0[i] = a0 ? (double)a0[i] : 0.0;
-    m = fmax(m, fabs(x1[i] - x0[i]));
-  }
+  for (int i = 0; i < 3; ++i) m = fmax(m, fmax(fabs((double)a1[i]), a0 ? fabs((double)a0[i]) : 0.0));
   int e = 0;
   (void)frexp(m, &e);  // m = 0 (a zero column): e = 0
-  bool ok = true;
+  bool ok = m < 0x1p1000;
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     // y = x + 1.5 2^52 rounds x to an integer, whose value is the difference
-    // of the bit patterns of y and 1.5 2^52.
-    const double p = ldexp(x1[i], 41 - e), q = ldexp(x0[i], 41 - e);
+    // of the bit patterns of y and 1.5 2^52.  (A NaN equals nothing.)
+    const double p = ldexp((double)a1[i], 41 - e), q = a0 ? ldexp((double)a0[i], 41 - e) : 0.0;
     const double yp = p + 0x1.8p52, yq = q + 0x1.8p52;
-    ok = ok && fabs(p) < 0x1p51 && fabs(q) < 0x1p51 && yp - 0x1.8p52 == p && yq - 0x1.8p52 == q;
+    ok = ok & (yp - 0x1.8p52 == p) & (yq - 0x1.8p52 == q);
     c[i] = __builtin_bit_cast(long long, yp) - __builtin_bit_cast(long long, yq);
   }
   return ok;
 }
 
-// Sign of det[a, b, c] for |entries| <= 2^41: the minors stay below 2^83.01 and
-// the determinant below 2^125.6.  A loop over the first column's entries,
-// rows rotated, to save registers and instructions.
+// Sign of det[a, b, c] for |entries| < 2^42, exactly, in digits of 30 bits, so
+// that every product is one of two 32-bit integers: entries h 2^30 + l with
+// |h| <= 2^12, minors m0 + m1 2^30 + m2 2^60 with |m2| < 2^26, and digit sums
+// of the determinant below 2^62.  (128-bit integers would have to carry from
+// product to product.)
 __host__ __device__ inline int int_det_sign(const long long* a, const long long* b, const long long* c) {
-  typedef __int128 i128;
-  long long a0 = a[0], a1 = a[1], a2 = a[2], b0 = b[0], b1 = b[1], b2 = b[2], c0 = c[0], c1 = c[1], c2 = c[2];
-  i128 d = 0;
-#pragma unroll 1
+  constexpr int kMask = (1 << 30) - 1;
+  int al[3], ah[3], bl[3], bh[3], cl[3], ch[3];
+#pragma unroll
   for (int i = 0; i < 3; ++i) {
-    d += (i128)a0 * ((i128)b1 * c2 - (i128)b2 * c1);
-    const long long ta = a0, tb = b0, tc = c0;
-    a0 = a1;
-    a1 = a2;
-    a2 = ta;
-    b0 = b1;
-    b1 = b2;
-    b2 = tb;
-    c0 = c1;
-    c1 = c2;
-    c2 = tc;
+    al[i] = (int)a[i] & kMask;
+    ah[i] = (int)(a[i] >> 30);
+    bl[i] = (int)b[i] & kMask;
+    bh[i] = (int)(b[i] >> 30);
+    cl[i] = (int)c[i] & kMask;
+    ch[i] = (int)(c[i] >> 30);
   }
-  return d > 0 ? 1 : (d < 0 ? -1 : 0);
+  long long d0 = 0, d1 = 0, d2 = 0, d3 = 0;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const int j = (i + 1) % 3, k = (i + 2) % 3;
+    const int nl = -bl[k], nh = -bh[k];
+    const long long s0 = (long long)bl[j] * cl[k] + (long long)nl * cl[j];
+    long long s1 = (long long)bl[j] * ch[k] + (long long)bh[j] * cl[k] + (long long)nl * ch[j] + (long long)nh * cl[j];
+    s1 += s0 >> 30;
+    const int m0 = (int)s0 & kMask, m1 = (int)s1 & kMask;
+    const int m2 = (int)((long long)bh[j] * ch[k] + (long long)nh * ch[j] + (s1 >> 30));
+    d0 += (long long)al[i] * m0;
+    d1 += (long long)al[i] * m1 + (long long)ah[i] * m0;
+    d2 += (long long)al[i] * m2 + (long long)ah[i] * m1;
+    d3 += (long long)ah[i] * m2;
+  }
+  d1 += d0 >> 30;
+  d2 += d1 >> 30;
+  d3 += d2 >> 30;
+  return d3 < 0 ? -1 : ((d3 | ((d0 | d1 | d2) & kMask)) != 0 ? 1 : 0);
 }
 
 // Float64 estimate of the same determinant with a certified error bound.
@@ -189,22 +201,25 @@ enum SignFlags : unsigned { kFlagExact = 1u, kFlagPerturbed = 2u };
 
 // The same sign from the filter or, behind it, the integers alone; 2 when
 // neither applies (a column without an integer form).
-__host__ __device__ inline int quick_det_diff_sign(const float* A1, const float* A0, const float* B1,
-                                                   const float* B0, const float* C1, const float* C0,
-                                                   unsigned* flags) {
-  int s = filtered_det_diff_sign(A1, A0, B1, B0, C1, C0);
+// p: A1, A0, B1, B0, C1, C0 (absent points as zeros).
+__host__ __device__ inline int quick_det_sign(const float (&p)[6][3], unsigned* flags) {
+  int s = filtered_det_diff_sign(p[0], p[1], p[2], p[3], p[4], p[5]);
   if (s != 2) return s;
   if (flags) *flags |= kFlagExact;
   long long a[3], b[3], c[3];
-  const bool ka = column_to_int(A1, A0, a);
-  const bool kb = column_to_int(B1, B0, b);
-  const bool kc = column_to_int(C1, C0, c);
-  return ka && kb && kc ? int_det_sign(a, b, c) : 2;
+  const bool ka = column_to_int(p[0], p[1], a);
+  const bool kb = column_to_int(p[2], p[3], b);
+  const bool kc = column_to_int(p[4], p[5], c);
+  return ka & kb & kc ? int_det_sign(a, b, c) : 2;
 }
 
 __host__ __device__ inline int det_diff_sign(const float* A1, const float* A0, const float* B1, const float* B0,
                                              const float* C1, const float* C0, unsigned* flags) {
-  const int s = quick_det_diff_sign(A1, A0, B1, B0, C1, C0, flags);
+  const float* const from[6] = {A1, A0, B1, B0, C1, C0};
+  float p[6][3];
+  for (int k = 0; k < 6; ++k)
+    for (int i = 0; i < 3; ++i) p[k][i] = from[k] ? from[k][i] : 0.f;
+  const int s = quick_det_sign(p, flags);
   return s != 2 ? s : expansion_det_diff_sign(A1, A0, B1, B0, C1, C0);
 }
 
@@ -215,23 +230,57 @@ __host__ __device__ inline int orient3d_sign(const float* a, const float* b, con
 
 // Sign of the edge (p, q) seen by the ray S -> P translated by eps U + eps^2 V:
 // det[P - S, p - S, q - S], else det[P - S, U, p - q], else det[P - S, V, p - q].
-// Zero only for an edge parallel to P - S.  kQuick: 2 when a determinant needs
-// the expansion (a walk that calls this loses the registers that it uses, so
-// the quick form makes no call of its own).
-template <bool kQuick>
+// Zero only for an edge parallel to P - S.  By the filter and the expansion,
+// which decide every input.
 __host__ __device__ inline int perturbed_edge_sign(const float* S, const float* P, const float* U, const float* V,
                                                    const float* p, const float* q, unsigned* flags) {
   const float *B1 = p, *B0 = S, *C1 = q, *C0 = S;
   int s = 0;
-#pragma unroll
+#pragma unroll 1
   for (int level = 0; level < 3; ++level) {
-    s = kQuick ? quick_det_diff_sign(P, S, B1, B0, C1, C0, flags) : det_diff_sign(P, S, B1, B0, C1, C0, flags);
+    s = filtered_det_diff_sign(P, S, B1, B0, C1, C0);
+    if (s == 2) {
+      *flags |= kFlagExact;
+      s = expansion_det_diff_sign(P, S, B1, B0, C1, C0);
+    }
     if (s != 0) break;
-    if (flags) *flags |= kFlagPerturbed;
+    *flags |= kFlagPerturbed;
     B1 = level == 0 ? U : V;
     B0 = nullptr;
     C1 = p;
     C0 = q;
+  }
+  return s;
+}
+
+// The same by the filter and the integers: 2 where a determinant has no integer
+// form.  One determinant in a loop over the levels, and no call: a walk has
+// this inline beside its step.
+__host__ __device__ inline int quick_perturbed_edge_sign(const float* S, const float* P, const float* U,
+                                                         const float* V, const float* p, const float* q,
+                                                         unsigned* flags) {
+  float x[6][3];
+  for (int i = 0; i < 3; ++i) {
+    x[0][i] = P[i];
+    x[1][i] = x[3][i] = x[5][i] = S[i];
+    x[2][i] = p[i];
+    x[4][i] = q[i];
+  }
+  int s = 0;
+#pragma unroll 1
+  for (int level = 0; level < 3; ++level) {
+    s = quick_det_sign(x, flags);
+    if (s != 0) break;
+    *flags |= kFlagPerturbed;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      if (level == 0) {
+        x[5][i] = x[4][i];
+        x[4][i] = x[2][i];
+        x[3][i] = 0.f;
+      }
+      x[2][i] = level == 0 ? U[i] : V[i];
+    }
   }
   return s;
 }

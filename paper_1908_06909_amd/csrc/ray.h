@@ -33,7 +33,8 @@ __device__ __forceinline__ int edge_sign_bits(float3 S, float3 P, float3 U, floa
   float s[3] = {S.x, S.y, S.z}, pp[3] = {P.x, P.y, P.z}, u[3] = {U.x, U.y, U.z}, v[3] = {V.x, V.y, V.z};
   float a[3] = {p.x, p.y, p.z}, b[3] = {q.x, q.y, q.z};
   unsigned flags = 0;
-  int sg = perturbed_edge_sign<kQuick>(s, pp, u, v, a, b, &flags);
+  const int sg = kQuick ? quick_perturbed_edge_sign(s, pp, u, v, a, b, &flags)
+                        : perturbed_edge_sign(s, pp, u, v, a, b, &flags);
   return (sg + 1) | (int)(flags << 2);
 }
 
@@ -45,8 +46,14 @@ __device__ __noinline__ int expansion_edge_sign(float3 S, float3 P, float3 U, fl
   return edge_sign_bits<false>(S, P, U, V, p, q);
 }
 
+// kInline: the quick form beside the caller's own code.  The walks' steps ask
+// for it (a call's register saves cost them more than the arithmetic); the
+// entry tests, with three places that ask, are slower with it (the entry faces
+// of 24^3 128x128x20 take 33 us with calls, 43 inline), and the element-driven
+// exact pass keeps its registers for itself.
+template <bool kInline = false>
 __device__ __forceinline__ int slow_edge_sign(float3 S, float3 P, float3 U, float3 V, float3 p, float3 q) {
-  int r = quick_edge_sign(S, P, U, V, p, q);
+  int r = kInline ? edge_sign_bits<true>(S, P, U, V, p, q) : quick_edge_sign(S, P, U, V, p, q);
   if (__builtin_expect((r & 3) == 3, 0)) r = expansion_edge_sign(S, P, U, V, p, q);
   return r;
 }

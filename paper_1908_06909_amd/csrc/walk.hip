@@ -160,7 +160,7 @@ __device__ __forceinline__ int resolve(int fast, const Ray& r, float3 p, float3 
 
 template <class Src, class St>
 __device__ __forceinline__ int resolve_src(const Src& q, float3 a, float3 b, St& st) {
-  int res = slow_edge_sign(q.S(), q.P(), q.U(), q.V(), a, b);
+  int res = slow_edge_sign<true>(q.S(), q.P(), q.U(), q.V(), a, b);
   st.add_fp64();
   if (res & (kFlagExact << 2)) st.add_exact();
   if (res & (kFlagPerturbed << 2)) st.add_pert();
@@ -747,7 +747,7 @@ __device__ __forceinline__ int fixed_scale_exp(const FixedScale& f) {
 // Every thread of the block must call it.
 // kCached: every ray's entry face comes from io.entry (the launch has an
 // entry cache), so the kernel carries no tree search.
-template <int MODE, bool kLeanSrc = false, bool kCached = false>
+template <int MODE, bool kCached = false>
 __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G, const TileMap& tm, int64_t block,
                                            int a0, int na_chunk, const BlockIO& io, int* tkeys,
                                            long long* tvals) {
@@ -869,20 +869,13 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
     flush_stats(M, st, rays);
   } else {
     const int64_t rid = ((int64_t)a * G.nv + j) * G.nu + i;
-    // The single-problem walks have registers to spare, so their exact paths
-    // read the ray from registers; the batched ones (and the windowed
-    // backprojection) re-read it from the frame.
-    using Src = typename std::conditional<kLeanSrc, PixelSrc, RegSrc>::type;
     Ray r{};
-    Src q{};
+    PixelSrc q{};
     WalkOut<MODE> o;
     int e = -1;
     if (active) {
       r = cone_ray(G, M.extent, a, i, j);
-      if constexpr (kLeanSrc)
-        q = pixel_src(G, a, i, j);
-      else
-        q = RegSrc{r.S, r.P, r.U, r.V};
+      q = pixel_src(G, a, i, j);
       if constexpr (kCached)
         e = io.entry[rid];
       else
@@ -912,9 +905,9 @@ __global__ __launch_bounds__(256, 4) void pixel_walk_kernel(MeshView M, GeomView
   if constexpr (MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeBackExact) {
     __shared__ int tkeys[kBlockWaves * kScatterSlots];
     __shared__ long long tvals[kBlockWaves * kScatterSlots];
-    walk_block<MODE, false, kCached>(M, G, tm, xcd_block(blockIdx.x, gridDim.x), a0, na_chunk, io, tkeys, tvals);
+    walk_block<MODE, kCached>(M, G, tm, xcd_block(blockIdx.x, gridDim.x), a0, na_chunk, io, tkeys, tvals);
   } else {
-    walk_block<MODE, false, kCached>(M, G, tm, xcd_block(blockIdx.x, gridDim.x), a0, na_chunk, io, nullptr,
+    walk_block<MODE, kCached>(M, G, tm, xcd_block(blockIdx.x, gridDim.x), a0, na_chunk, io, nullptr,
                                      nullptr);
   }
 }
@@ -1170,9 +1163,9 @@ __global__ __launch_bounds__(256, 4) void batch_walk_kernel(const BatchDesc* __r
     if constexpr (MODE == kModeBackAtomic) {
       __shared__ int tkeys[kBlockWaves * kScatterSlots];
       __shared__ long long tvals[kBlockWaves * kScatterSlots];
-      walk_block<MODE, true, true>(d.M, d.G, d.tm, block, 0, d.G.na, io, tkeys, tvals);
+      walk_block<MODE, true>(d.M, d.G, d.tm, block, 0, d.G.na, io, tkeys, tvals);
     } else {
-      walk_block<MODE, true, true>(d.M, d.G, d.tm, block, 0, d.G.na, io, nullptr, nullptr);
+      walk_block<MODE, true>(d.M, d.G, d.tm, block, 0, d.G.na, io, nullptr, nullptr);
     }
   }
 }
