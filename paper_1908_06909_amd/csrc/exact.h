@@ -210,7 +210,7 @@ __host__ __device__ inline int quick_det_sign(const float (&p)[6][3], unsigned* 
   const bool ka = column_to_int(p[0], p[1], a);
   const bool kb = column_to_int(p[2], p[3], b);
   const bool kc = column_to_int(p[4], p[5], c);
-  return ka & kb & kc ? int_det_sign(a, b, c) : 2;
+  return (ka & kb & kc) ? int_det_sign(a, b, c) : 2;
 }
 
 __host__ __device__ inline int det_diff_sign(const float* A1, const float* A0, const float* B1, const float* B0,

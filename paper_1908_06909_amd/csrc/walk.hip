@@ -338,7 +338,8 @@ template <int kSlots>
 __device__ __forceinline__ unsigned table_home(int tet) {
   static_assert(kSlots < (1 << 12), "slot index times 2^20 must fit 32 bits");
   static_assert(kSlots % (1 << kGroupBits) == 0, "whole groups");
-  const unsigned h = __umul24(((unsigned)tet >> kGroupBits) & 0xFFFFFFu, 0x9E3779u);
+  unsigned h;  // a 24-bit product; as an ordinary one it becomes a full 32-bit multiplication
+  asm("v_mul_u32_u24 %0, %1, %2" : "=v"(h) : "s"(0x9E3779u), "v"((unsigned)tet >> kGroupBits));
   return (((((h >> 4) & 0xFFFFFu) * (unsigned)(kSlots >> kGroupBits)) >> 20) << kGroupBits) |
          ((unsigned)tet & ((1u << kGroupBits) - 1u));
 }
@@ -346,7 +347,7 @@ __device__ __forceinline__ unsigned table_home(int tet) {
 template <int kSlots>
 __device__ __forceinline__ unsigned next_slot(unsigned slot) {
   const unsigned s = slot + (1u << kGroupBits);
-  return s >= (unsigned)kSlots ? s - (unsigned)kSlots : s;
+  return (kSlots & (kSlots - 1)) == 0 ? s & (unsigned)(kSlots - 1) : s >= (unsigned)kSlots ? s - (unsigned)kSlots : s;
 }
 
 // x rounded to the nearest integer (ties to even), |x| < 2^51: in float64,
@@ -361,33 +362,37 @@ __device__ __forceinline__ long long round_to_i64(float x) {
   return (long long)(((unsigned long long)(unsigned)hi << 32) | lo);
 }
 
-// Adds the fixed-point term m to the slot of `tet`; false when the
-// tetrahedron finds no slot within kLdsProbes probes (the caller then adds
-// the term elsewhere).  `slot` is the key's home slot and `claimed` what the
-// compare-and-swap that claimed it for `tet` returned, issued when the ray
-// entered the tetrahedron (a slot keeps its key until the window's flush):
-// -1 or `tet` mean the home slot is the tetrahedron's.
-template <int kSlots>
-__device__ __forceinline__ bool lds_accumulate(lds_i32* keys, lds_i64* vals, int tet, long long m, unsigned slot,
-                                               int claimed) {
-  int k = claimed;
-  if (k != -1 && k != tet) {
-    // The first probe is written out: it settles nearly every displaced key,
-    // and the loop's bookkeeping then only runs when it fails.
-    slot = next_slot<kSlots>(slot);
-    k = lds_cas(keys + slot, tet);
-    if (k != -1 && k != tet) {
+// Adds the fixed-point term m to the slot of `tet`, in every active lane.
+// `slot` is the key's home slot and `claimed` what the compare-and-swap that
+// claimed it for `tet` returned, issued when the ray entered the tetrahedron
+// (a slot keeps its key until the window's flush): -1 or `tet` mean the home
+// slot is the tetrahedron's.  A lane whose tetrahedron finds no slot within
+// kLdsProbes probes calls `elsewhere` and adds zero to the last slot probed.
+template <int kSlots, class Elsewhere>
+__device__ __forceinline__ void lds_accumulate(lds_i32* keys, lds_i64* vals, int tet, long long m, unsigned slot,
+                                               int claimed, Elsewhere&& elsewhere) {
+  const unsigned long long displaced = __ballot(claimed != -1) & __ballot(claimed != tet);
+  if (displaced != 0) {
+    if (__builtin_amdgcn_inverse_ballot_w64(displaced)) {
+      // The first probe is written out: it settles nearly every displaced key,
+      // and the loop's bookkeeping then only runs when it fails.
+      slot = next_slot<kSlots>(slot);
+      int k = lds_cas(keys + slot, tet);
+      if (__builtin_expect(k != -1 && k != tet, 0)) {
 #pragma unroll 1
-      for (int p = 2; p < kLdsProbes; ++p) {
-        slot = next_slot<kSlots>(slot);
-        k = lds_cas(keys + slot, tet);
-        if (k == -1 || k == tet) break;
+        for (int p = 2; p < kLdsProbes; ++p) {
+          slot = next_slot<kSlots>(slot);
+          k = lds_cas(keys + slot, tet);
+          if (k == -1 || k == tet) break;
+        }
+        if (k != -1 && k != tet) {
+          elsewhere();
+          m = 0;
+        }
       }
-      if (k != -1 && k != tet) return false;
     }
   }
   __hip_atomic_fetch_add(vals + slot, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-  return true;
 }
 
 // Adds the partial sum m 2^-scale to tetrahedron tet's exact sum.
@@ -424,7 +429,7 @@ struct WalkOut {
 // Walk state between steps: the entry face as three vertex slots, the
 // fourth vertex v, the current tetrahedron and the ray parameter where the
 // ray entered it.  `loc` holds the local indices (0..3 within the current
-// tetrahedron) of slots 0, 1, 2 and of v in four 2-bit fields of one byte.
+// tetrahedron) of slots 0, 1, 2 in three 2-bit fields.
 //
 // Crossing face f (the face opposite local vertex f) into a neighbour whose
 // opposite vertex has local index `back` there, the three shared vertices
@@ -445,29 +450,36 @@ struct WalkState {
   bool far;
 };
 
-// Local-index remap as a table of loc_remap_entry (common.h), one byte per
-// (loc, k, back), copied into each block's LDS: a read per step, in place of
-// about fifteen vector instructions.
+// Local-index remap as a table of loc_remap_entry (common.h) without v's field,
+// which follows from the other three: one byte at loc << 4 | k << 2 | back,
+// copied into each block's LDS.  A read per step, in place of about fifteen
+// vector instructions.
+constexpr int kRemapRows = 64 * 4;
 struct alignas(4) LocRemap {
-  unsigned char v[kLocRemapEntries];
+  unsigned char v[kRemapRows * 4];
 };
 
 constexpr LocRemap make_loc_remap() {
   LocRemap t{};
-  for (unsigned i = 0; i < (unsigned)kLocRemapEntries; ++i) t.v[i] = (unsigned char)loc_remap_entry(i);
+  for (unsigned loc = 0; loc < 64; ++loc)
+    for (unsigned k = 0; k < 3; ++k)
+      for (unsigned back = 0; back < 4; ++back) {
+        const unsigned v = (6u - (loc & 3u) - (loc >> 2 & 3u) - (loc >> 4)) & 3u;
+        t.v[(loc * 4 + k) * 4 + back] = (unsigned char)(loc_remap_entry(((loc | v << 6) * 3 + k) * 4 + back) & 0x3Fu);
+      }
   return t;
 }
 
 __constant__ LocRemap kLocRemap = make_loc_remap();
 
-__shared__ __align__(4) unsigned char s_loc_remap[kLocRemapEntries];
+__shared__ __align__(4) unsigned char s_loc_remap[kRemapRows * 4];
 
 // Copies the remap table into the block's LDS; every thread of the block
 // calls it before its first step.
 __device__ __forceinline__ void load_loc_remap() {
   const unsigned* src = reinterpret_cast<const unsigned*>(kLocRemap.v);
   unsigned* dst = reinterpret_cast<unsigned*>(s_loc_remap);
-  for (int i = threadIdx.x; i < kLocRemapEntries / 4; i += blockDim.x) dst[i] = src[i];
+  for (int i = threadIdx.x; i < kRemapRows; i += blockDim.x) dst[i] = src[i];
   __syncthreads();
 }
 
@@ -479,7 +491,7 @@ __device__ __forceinline__ void walk_start(const MeshView& M, const Ray& r, cons
   const float4* bq = M.bfaces + 4 * (size_t)entry;
   float4 q0 = bq[0], q1 = bq[1], q2 = bq[2], q3 = bq[3];
   w.packed = __float_as_int(q0.w) << 2;
-  w.loc = (unsigned)__float_as_int(q1.w) & 0xFFu;
+  w.loc = (unsigned)__float_as_int(q1.w) & 0x3Fu;
   w.a0 = make_float3(q0.x, q0.y, q0.z);
   w.a1 = make_float3(q1.x, q1.y, q1.z);
   w.a2 = make_float3(q2.x, q2.y, q2.z);
@@ -505,13 +517,20 @@ __device__ __forceinline__ void walk_start(const MeshView& M, const Ray& r, cons
 // products and moves issue in about half the time of selects, fused
 // multiply-adds and float64 operations.  Hence the signs as wavefront masks,
 // combined in scalar registers; edges subtracted anew rather than selected;
-// and one bound for all edges of the mesh in place of each step's own.  96
-// vector instructions a step instead of 129: 90 angles of the benchmark
-// forward 15.1 -> 13.3 ms, atomic backprojection 20.2 -> 18.1 (from a mesh
-// seen by few rays, where memory is the bound, as before: 6.4 and 15.8).
+// and one bound for all edges of the mesh in place of each step's own.  Rare
+// cases are branches of the whole wavefront on such masks, which then name the
+// lanes concerned: a branch per lane writes the execution mask twice, also
+// where no lane takes it (moving v into its slot under three masks, in place
+// of nine selects, is slower by 7%).  90 angles of the benchmark, forward and
+// atomic backprojection: 15.1 and 20.2 ms with 129 vector instructions a step
+// and a branch per lane, 13.3 and 18.1 with 96, 12.8 and 17.2 with 89 and
+// the wavefront's branches (from a mesh seen by few rays, where memory is the
+// bound, as before: 6.4 and 15.8).
+//
+// `live`: the lanes that take the step, all those that call it.
 template <int MODE, class Src, class St>
 __device__ __forceinline__ void walk_step(const MeshView& M, const Ray& r, const Src& q, WalkState& w,
-                                          WalkOut<MODE>& o, St& st) {
+                                          WalkOut<MODE>& o, St& st, unsigned long long live) {
   constexpr bool kTable = MODE == kModeBackAtomic || MODE == kModeBackFixed || MODE == kModeBackExact;
   const float3 v = w.v;
   const int tet = w.packed >> 2;
@@ -524,41 +543,47 @@ __device__ __forceinline__ void walk_step(const MeshView& M, const Ray& r, const
   // E(v, a_{k+2}) are - and +; of three signs that are not all the same,
   // exactly one pair is.
   const unsigned long long n0 = __ballot(g.E0 < 0.f), n1 = __ballot(g.E1 < 0.f), n2 = __ballot(g.E2 < 0.f);
-  bool k0 = __builtin_amdgcn_inverse_ballot_w64(n1 & ~n2), k1 = __builtin_amdgcn_inverse_ballot_w64(n2 & ~n0),
-       k2 = __builtin_amdgcn_inverse_ballot_w64(n0 & ~n1);
+  unsigned long long m0 = n1 & ~n2, m1 = n2 & ~n0, m2 = n0 & ~n1;  // lanes that leave opposite slot 0, 1, 2
+  const unsigned long long ok = __ballot(step_signs_certain(g, M.edge_max)) & (m0 | m1 | m2);
+  unsigned long long dead = 0;  // lanes whose walk fails here
   // (The branches that call out are marked as unlikely: the registers that a
   // call clobbers are then saved around it, not moved out of the whole loop.)
-  if (__builtin_expect(!(step_signs_certain(g, M.edge_max) & (k0 | k1 | k2)), 0)) {
-    int k = step_exit_common(g);
-    if (k < 0) {
-      // Each edge under its own bound, then in float64 or exactly.  One place
-      // that calls out, in a loop over the edges.
-      int s0 = step_edge_certified(g.E0, g.m0, g.K);
-      int s1 = step_edge_certified(g.E1, g.m1, g.K);
-      int s2 = step_edge_certified(g.E2, g.m2, g.K);
+  if (__builtin_expect(ok != live, 0)) {
+    int k = -2;
+    if (!__builtin_amdgcn_inverse_ballot_w64(ok)) {
+      k = step_exit_common(g);
+      if (k < 0) {
+        // Each edge under its own bound, then in float64 or exactly.  One place
+        // that calls out, in a loop over the edges.
+        int s0 = step_edge_certified(g.E0, g.m0, g.K);
+        int s1 = step_edge_certified(g.E1, g.m1, g.K);
+        int s2 = step_edge_certified(g.E2, g.m2, g.K);
 #pragma unroll 1
-      for (int i = 0; i < 3; ++i) {
-        if ((i == 0 ? s0 : i == 1 ? s1 : s2) != 0) continue;
-        const float3 a = make_float3(i == 0 ? w.a0.x : i == 1 ? w.a1.x : w.a2.x,
-                                     i == 0 ? w.a0.y : i == 1 ? w.a1.y : w.a2.y,
-                                     i == 0 ? w.a0.z : i == 1 ? w.a1.z : w.a2.z);
-        const int sg = resolve_src(q, v, a, st);
-        s0 = i == 0 ? sg : s0;
-        s1 = i == 1 ? sg : s1;
-        s2 = i == 2 ? sg : s2;
+        for (int i = 0; i < 3; ++i) {
+          if ((i == 0 ? s0 : i == 1 ? s1 : s2) != 0) continue;
+          const float3 a = make_float3(i == 0 ? w.a0.x : i == 1 ? w.a1.x : w.a2.x,
+                                       i == 0 ? w.a0.y : i == 1 ? w.a1.y : w.a2.y,
+                                       i == 0 ? w.a0.z : i == 1 ? w.a1.z : w.a2.z);
+          const int sg = resolve_src(q, v, a, st);
+          s0 = i == 0 ? sg : s0;
+          s1 = i == 1 ? sg : s1;
+          s2 = i == 2 ? sg : s2;
+        }
+        k = exit_slot(s0, s1, s2);
       }
-      k = exit_slot(s0, s1, s2);
+      if (k == 3) {
+        // The rest of the step adds zero for this lane, and the zero ends it.
+        g.D = make_float3(0.f, 0.f, 0.f);
+        x = 0.f;
+      }
     }
-    if (k == 3) {
-      st.add_failed();
-      st.take_back_step();
-      w.packed = -1;
-      return;
-    }
-    k0 = k == 0;
-    k1 = k == 1;
-    k2 = k == 2;
+    m0 = (m0 & ok) | __ballot(k == 0);
+    m1 = (m1 & ok) | __ballot(k == 1);
+    m2 = (m2 & ok) | __ballot(k == 2);
+    dead = __ballot(k == 3);
   }
+  const bool k0 = __builtin_amdgcn_inverse_ballot_w64(m0), k1 = __builtin_amdgcn_inverse_ballot_w64(m1),
+             k2 = __builtin_amdgcn_inverse_ballot_w64(m2);
   // Next tetrahedron across the exit face (its local index is in slot k's
   // field of loc): the record's load is issued as soon as the face is known,
   // so that its latency overlaps the crossing and the segment's accumulation.
@@ -571,18 +596,20 @@ __device__ __forceinline__ void walk_step(const MeshView& M, const Ray& r, const
   w.a2 = make_float3(k2 ? v.x : w.a2.x, k2 ? v.y : w.a2.y, k2 ? v.z : w.a2.z);
   const float3 n = f3cross(f3sub(w.a1, w.a0), f3sub(w.a2, w.a0));
   const float den = f3dot(r.d, n);
-  float dt;
-  if (__builtin_expect(fabsf(den) > r.gd * fmaxf(fabsf(n.x), fmaxf(fabsf(n.y), fabsf(n.z))), 1)) {
-    dt = f3dot(g.D, n) * __builtin_amdgcn_rcpf(den);  // (v is on the face); v_rcp_f32, about 1 ulp
-  } else {
-    st.add_grazing();
-    dt = (float)(crossing_s_fp64(q.S(), q.P(), w.a0, w.a1, w.a2) - w.s_in);
+  float dt = f3dot(g.D, n) * __builtin_amdgcn_rcpf(den);  // (v is on the face); v_rcp_f32, about 1 ulp
+  const unsigned long long grazing =
+      __ballot(!(fabsf(den) > r.gd * fmaxf(fabsf(n.x), fmaxf(fabsf(n.y), fabsf(n.z)))));
+  if (__builtin_expect(grazing != 0, 0)) {
+    if (__builtin_amdgcn_inverse_ballot_w64(grazing & ~dead)) {
+      st.add_grazing();
+      dt = (float)(crossing_s_fp64(q.S(), q.P(), w.a0, w.a1, w.a2) - w.s_in);
+    }
   }
   if (__builtin_expect(w.far, 1))  // (1, the whole ray's parameter range, is an inline constant)
     dt = __builtin_amdgcn_fmed3f(dt, 0.0f, 1.0f);
   else
     dt = __builtin_amdgcn_fmed3f(dt, 0.0f, (float)fmax(0.5 - w.s_in, 0.0));
-  if (__builtin_expect(dt == 0.f, 0)) st.add_zero();
+  const unsigned long long zero = __ballot(dt == 0.f);
   if constexpr (MODE == kModeForward) {
     o.acc = fma((double)dt, (double)x, o.acc);  // the product is exact
   } else if constexpr (kTable) {
@@ -591,7 +618,7 @@ __device__ __forceinline__ void walk_step(const MeshView& M, const Ray& r, const
     // per step, and the step's claim is then consumed on every path.
     const float t = dt * o.weight;  // in units of 2^-scale_exp
     const long long m = round_to_i64(t);
-    if (!lds_accumulate<kScatterSlots>(o.lds_keys, o.lds_vals, tet, m, w.home, w.claim)) {
+    lds_accumulate<kScatterSlots>(o.lds_keys, o.lds_vals, tet, m, w.home, w.claim, [&] {
       if constexpr (MODE == kModeBackFixed) {
         atomicAdd(o.acc64 + tet, (unsigned long long)m);
       } else if constexpr (MODE == kModeBackExact) {
@@ -599,18 +626,20 @@ __device__ __forceinline__ void walk_step(const MeshView& M, const Ray& r, const
       } else {
         unsafeAtomicAdd(o.xhat + tet, ldexpf(t, -o.scale_exp));
       }
-    }
+    });
   } else if constexpr (MODE == kModeBackDirect) {
     if (dt > 0.f) unsafeAtomicAdd(o.xhat + tet, dt * o.weight);
   } else if constexpr (MODE == kModeCountAll) {
-    o.count++;
+    o.count += __builtin_amdgcn_inverse_ballot_w64(dead) ? 0 : 1;
   } else if constexpr (MODE == kModeTrace) {
-    o.out_tet[o.cursor] = o.perm[tet];
-    o.out_len[o.cursor] = dt * r.dn;
-    o.cursor++;
+    if (!__builtin_amdgcn_inverse_ballot_w64(dead)) {
+      o.out_tet[o.cursor] = o.perm[tet];
+      o.out_len[o.cursor] = dt * r.dn;
+      o.cursor++;
+    }
   }
   w.s_in += (double)dt;  // float64: no rounding drift along the ray
-  unsigned R = __umul24(L, 12u) + sh * 2u;  // the remap's row (loc, k)
+  unsigned R = (L << 4) | (sh << 1);  // the remap's row (loc, k)
   // What does not need the record is done while it is in flight.  (An empty
   // statement that takes these values, so the compiler computes them here
   // rather than sinking them behind the wait for the record.)
@@ -622,9 +651,19 @@ __device__ __forceinline__ void walk_step(const MeshView& M, const Ray& r, const
   asm volatile("" : "+v"(rec.x), "+v"(rec.y), "+v"(rec.z), "+v"(rec.w));
   w.packed = __float_as_int(rec.x);
   w.v = xyz(rec);
-  if (w.packed < 0) return;
-  // Read back while the next step computes; needed at its exit face.
-  w.loc = s_loc_remap[R + ((unsigned)w.packed & 3u)];
+  if (__builtin_expect(zero != 0, 0)) {
+    if (__builtin_amdgcn_inverse_ballot_w64(dead)) {
+      st.add_failed();
+      st.take_back_step();
+      w.packed = -1;
+    } else if (__builtin_amdgcn_inverse_ballot_w64(zero)) {
+      st.add_zero();
+    }
+  }
+  // Read back while the next step computes; needed at its exit face.  (A ray
+  // that has ended has -1 here: its read and its claim, of the empty key, change
+  // nothing, and cost less than a branch.)
+  w.loc = s_loc_remap[R | ((unsigned)w.packed & 3u)];
   // Table walks claim the new tetrahedron's home slot now; the old key comes
   // back while the next step computes, and is needed only at its end.
   if constexpr (kTable) {
@@ -644,7 +683,7 @@ __device__ __forceinline__ int walk_steps(const MeshView& M, const Ray& r, const
     const unsigned long long live = __ballot(w.packed >= 0);
     if (!live) break;
     segments += __popcll(live);
-    if (w.packed >= 0) walk_step<MODE>(M, r, q, w, o, st);
+    if (w.packed >= 0) walk_step<MODE>(M, r, q, w, o, st, live);
   }
   return segments;
 }
