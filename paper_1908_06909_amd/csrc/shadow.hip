@@ -76,6 +76,7 @@ struct ShadowArgs {
   float eps_p;       // bound on the detector-plane distance between a pixel's ray and the pixel centre
   int* dirty_count;  // items (chunk * nt + t) left to the exact pass
   int* dirty;
+  const double* frames;  // [na][kFrameValues], from angle a0 on
 };
 
 struct ShadowStats {
@@ -131,6 +132,43 @@ __device__ __forceinline__ void project_vertex(const FrameD& F, float3 p, double
   be = F.g01 * xu + F.g11 * xv;
 }
 
+// What the fast pass needs of an angle, the same for all elements: S, N / hN,
+// the dual axes U*, V* (alpha = U* . X for X = alpha U + beta V), U* . (S - D),
+// V* . (S - D) and the sign of hN.  Computed once a launch: every wavefront
+// computing it for itself spent 130 of its 580 set-up instructions there.
+constexpr int kFrameValues = 16;
+
+__global__ void shadow_prepare_kernel(ShadowArgs A, double* frames) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k == 0) *A.dirty_count = 0;
+  if (k >= A.na) return;
+  const FrameD F = load_frame(A.G.frame, A.a0 + k);
+  const double U[3] = {F.U.x, F.U.y, F.U.z}, V[3] = {F.V.x, F.V.y, F.V.z};
+  const double SD[3] = {F.SDx, F.SDy, F.SDz}, N[3] = {F.Nx, F.Ny, F.Nz}, S[3] = {F.Sx, F.Sy, F.Sz};
+  double* o = frames + (size_t)kFrameValues * k;
+  double au = 0.0, av = 0.0;
+  for (int c = 0; c < 3; ++c) {
+    const double us = F.g00 * U[c] + F.g01 * V[c], vs = F.g01 * U[c] + F.g11 * V[c];
+    o[c] = S[c];
+    o[3 + c] = N[c] / F.hN;
+    o[6 + c] = us;
+    o[9 + c] = vs;
+    au += us * SD[c];
+    av += vs * SD[c];
+  }
+  o[12] = au;
+  o[13] = av;
+  o[14] = F.hN > 0.0 ? 1.0 : -1.0;
+  o[15] = 0.0;
+}
+
+// 1 / x to a few float64 roundings (v_rcp_f64 and two Newton steps).
+__device__ __forceinline__ double recip_f64(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
 __device__ __forceinline__ float3 tet_vertex(const float4* tq, int k) {
   const float* c = (const float*)tq + 3 * k;
   return make_float3(c[0], c[1], c[2]);
@@ -152,14 +190,14 @@ __device__ __forceinline__ int entry_face(int neg, int pos) {
 
 // Float64 3-D edge value E(p, q) = d . ((p - S) x (q - p)) with its filter;
 // returns +1 / -1 when certain, 0 when not.
-__device__ __forceinline__ int edge_sign_fp64(const FrameD& F, double dx, double dy, double dz, float dinf, float3 p,
-                                              float3 q, double* Eout) {
-  double rx = (double)p.x - F.Sx, ry = (double)p.y - F.Sy, rz = (double)p.z - F.Sz;
+__device__ __forceinline__ int edge_sign_fp64(float3 S, double dx, double dy, double dz, float dinf, float3 p, float3 q,
+                                              double* Eout) {
+  double rx = (double)p.x - S.x, ry = (double)p.y - S.y, rz = (double)p.z - S.z;
   double ex = (double)q.x - p.x, ey = (double)q.y - p.y, ez = (double)q.z - p.z;
   double cx = ry * ez - rz * ey, cy = rz * ex - rx * ez, cz = rx * ey - ry * ex;
   double E = fma(dx, cx, fma(dy, cy, dz * cz));
   if (Eout) *Eout = E;
-  float3 rf = f3sub(p, F.S), ef = f3sub(q, p);
+  float3 rf = f3sub(p, S), ef = f3sub(q, p);
   float m = (fabsf(rf.x) + fabsf(rf.y) + fabsf(rf.z)) * (fabsf(ef.x) + fabsf(ef.y) + fabsf(ef.z));
   float B = fmaf(dinf * kShadowRel, m, kShadowAbs);
   float Ef = (float)E;
@@ -247,6 +285,17 @@ __device__ __forceinline__ void face_min(const float* E, float* g) {
 // positive (no entry face: miss) or, for a hit, certainly negative with an
 // exit face whose smallest value is certainly positive; anything else takes
 // the per-edge route (float64 3-D values, then the exact pass).
+//
+// Bound by the issue of vector instructions, about 4.2 cycles each (reading no
+// projection values or no face planes changes its time by 3%): 400 an element
+// and angle, 120 a turn of the pixel loop and, in one turn of fourteen (of
+// seven with 4.5 eps_p Lb in the bound), 140 of the per-edge route.  Hence one
+// loop over the pixels of
+// all rows, branches of the whole wavefront on masks for what is rare, the
+// angle's values from a table, and the bound from the element's own extent.
+// 60 angles of 256 x 256 through 48^3 x 6 elements 5.7 -> 4.0 ms, 45 of
+// 512 x 512 through 64^3 x 6 18.6 -> 13.4, 100 of 64 x 64, hardly a pixel an
+// element, 3.27 -> 2.20.
 template <bool kLdsTable>
 __global__ __launch_bounds__(kShadowThreads, 4) void shadow_fast_kernel(ShadowArgs A) {
   // Face planes of each lane's tetrahedron, float64: (n_x, n_y) and
@@ -288,10 +337,20 @@ __global__ __launch_bounds__(kShadowThreads, 4) void shadow_fast_kernel(ShadowAr
     bool deferred = false;
 #pragma unroll 1
     for (int a = a_begin; a < a_end && !deferred; ++a) {
-      FrameD F = load_frame(A.G.frame, a);
-      double al[4], be[4];
+      const double* fr = A.frames + (size_t)kFrameValues * (a - A.a0);
+      const float* ff = A.G.frame + 12 * a;
+      const float3 S = make_float3(ff[0], ff[1], ff[2]);
+      double al[4], be[4], r0[3], r1[3];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) project_vertex(F, tet_vertex(tq, k), al[k], be[k]);
+      for (int k = 0; k < 4; ++k) {
+        const float3 p = tet_vertex(tq, k);
+        const double rx = (double)p.x - fr[0], ry = (double)p.y - fr[1], rz = (double)p.z - fr[2];
+        const double tau = recip_f64(fma(rx, fr[3], fma(ry, fr[4], rz * fr[5])));
+        al[k] = fma(tau, fma(rx, fr[6], fma(ry, fr[7], rz * fr[8])), fr[12]);
+        be[k] = fma(tau, fma(rx, fr[9], fma(ry, fr[10], rz * fr[11])), fr[13]);
+        if (k == 0) r0[0] = rx, r0[1] = ry, r0[2] = rz;
+        if (k == 1) r1[0] = rx, r1[1] = ry, r1[2] = rz;
+      }
       int i0, i1, j0, j1;
       if (!shadow_box(A, al, be, i0, i1, j0, j1)) continue;
       // Local detector coordinates around the pixel centre (i0, j0).
@@ -307,10 +366,19 @@ __global__ __launch_bounds__(kShadowThreads, 4) void shadow_fast_kernel(ShadowAr
       // E'_pq = (x_p - x)(y_q - y) - (y_p - y)(x_q - x) differs from its
       // exact value at the pixel centre by at most 34 u Lb^2 for the
       // rounding of the local coordinates (vertices and pixel) and of the
-      // affine evaluation; the ray meets the plane within eps_p of the
-      // centre, which moves E' by at most 4 eps_p Lb.
-      const float bound = fmaf(64.0f * kUnit * Lb, Lb, fmaf(4.5f * A.eps_p, Lb, kShadowAbs));
-      const float sg = F.hN > 0.0 ? 1.0f : -1.0f;
+      // affine evaluation.  The ray meets the plane within eps_p of the
+      // centre, and E' is affine in the pixel position, with slopes y_q - y_p
+      // and x_p - x_q: that moves it by at most eps_p times the sum of the
+      // largest of both, which is far more than the rounding (an element of 5
+      // pixels: 20 times) and decides how many pixels take the per-edge route.
+      float ex = 0.f, ey = 0.f;
+#pragma unroll
+      for (int e = 0; e < 6; ++e) {
+        ex = fmaxf(ex, fabsf(xk[kEdgeQ[e]] - xk[kEdgeP[e]]));
+        ey = fmaxf(ey, fabsf(yk[kEdgeP[e]] - yk[kEdgeQ[e]]));
+      }
+      const float bound = fmaf(64.0f * kUnit * Lb, Lb, fmaf(1.125f * A.eps_p, ex + ey, kShadowAbs));
+      const float sg = (float)fr[14];
       // E = sg E' = cC + kx cA + y cB with kx = i - i0 and y = (j - j0) dv.
       float cA[6], cB[6], cC[6];
 #pragma unroll
@@ -322,10 +390,10 @@ __global__ __launch_bounds__(kShadowThreads, 4) void shadow_fast_kernel(ShadowAr
       }
 #pragma unroll
       for (int f = 0; f < 4; ++f) {
-        const float3 pa = tet_vertex(tq, f == 0 ? 1 : 0);
+        const double* r = f == 0 ? r1 : r0;
         const double2 n0 = s_plane[f][0][lane];
         double2 n1 = s_plane[f][1][lane];
-        n1.y = ((double)pa.x - F.Sx) * n0.x + ((double)pa.y - F.Sy) * n0.y + ((double)pa.z - F.Sz) * n1.x;
+        n1.y = fma(r[0], n0.x, fma(r[1], n0.y, r[2] * n1.x));
         s_plane[f][1][lane] = n1;
       }
       // Row spans.  The shadow is bounded by the silhouette edges: those
@@ -334,7 +402,11 @@ __global__ __launch_bounds__(kShadowThreads, 4) void shadow_fast_kernel(ShadowAr
       // they leave by.  For a silhouette edge with outward sign s in its
       // entry face the whole shadow has s E_e <= 0, so a pixel with
       // s E_e > bound is no hit; in a row that bounds kx from one side:
-      // kx <= t or kx >= t with t = (s bound - R_e) / cA_e.  With a face seen
+      // kx <= t or kx >= t with t = (s bound - cC - y cB) / cA = tA + y tB,
+      // whose rounding is worth less than 16 u Lb^2 of E_e (|cC| and |y cB| are
+      // at most 2 Lb^2) beside the 34 of the bound's 64 that E_e itself needs.
+      // A silhouette has three or four edges, so at most three bound kx from
+      // each side.  With a face seen
       // nearly edge-on (|S_f| <= bound) the silhouette is uncertain and the
       // whole box is scanned; near-horizontal edges (|cA_e| < bound / 1024)
       // are not used.  Skipping pixels never changes a decision: every
@@ -342,67 +414,90 @@ __global__ __launch_bounds__(kShadowThreads, 4) void shadow_fast_kernel(ShadowAr
       const float Sf[4] = {cC[3] + cC[5] - cC[4], cC[2] - cC[5] - cC[1], cC[0] + cC[4] - cC[2],
                            cC[1] - cC[3] - cC[0]};
       const bool spans = fminf(fminf(fabsf(Sf[0]), fabsf(Sf[1])), fminf(fabsf(Sf[2]), fabsf(Sf[3]))) > bound;
-      float rA[6], sb[6];
-      bool upper[6], lower[6];
+      const float box_hi = (float)(i1 - i0);
+      // Slack for the rounding of t within the box and of the comparison.
+      const float slack = fmaf(box_hi, 0x1p-21f, 0x1p-10f);
+      float uA[3], uB[3], lA[3], lB[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        uA[k] = box_hi;
+        lA[k] = 0.f;
+        uB[k] = lB[k] = 0.f;
+      }
 #pragma unroll
       for (int e = 0; e < 6; ++e) {
         const bool fa = Sf[kEdgeFaceA[e]] < 0.f, fb = Sf[kEdgeFaceB[e]] < 0.f;
         const float sgn = fa ? kEdgeSignA[e] : -kEdgeSignA[e];
         const float g = sgn * cA[e];
         const bool use = spans && fa != fb && fabsf(cA[e]) * 1024.0f >= bound;
-        upper[e] = use && g > 0.f;
-        lower[e] = use && g < 0.f;
-        rA[e] = use ? 1.0f / cA[e] : 0.f;
-        sb[e] = sgn * bound;
+        const float rA = __builtin_amdgcn_rcpf(cA[e]);
+        const float tA = (sgn * bound - cC[e]) * rA, tB = -cB[e] * rA;
+        const bool upper = use && g > 0.f, lower = use && g < 0.f;
+        uA[2] = upper ? uA[1] : uA[2];
+        uB[2] = upper ? uB[1] : uB[2];
+        uA[1] = upper ? uA[0] : uA[1];
+        uB[1] = upper ? uB[0] : uB[1];
+        uA[0] = upper ? tA + slack : uA[0];
+        uB[0] = upper ? tB : uB[0];
+        lA[2] = lower ? lA[1] : lA[2];
+        lB[2] = lower ? lB[1] : lB[2];
+        lA[1] = lower ? lA[0] : lA[1];
+        lB[1] = lower ? lB[0] : lB[1];
+        lA[0] = lower ? tA - slack : lA[0];
+        lB[0] = lower ? tB : lB[0];
       }
-      const float box_hi = (float)(i1 - i0);
       const float* yrow = A.proj + (size_t)a * nv * nu;
+      // The pixels of all rows in one loop, each lane going to its next row
+      // when its span is through: lanes wait for the longest shadow, not for
+      // the longest span of every row (28 turns instead of 44 for the 18
+      // pixels of a 48^3 mesh's shadows on 256 columns, 62 instead of 92 for
+      // the 39 of 64^3 on 512).
+      int j = j0 - 1, k = 0, k_hi = -1;  // row, column and the span's last column, columns from i0
+      float R[6] = {}, vv = 0.f;
+      int64_t row = (int64_t)j * nu + i0;  // of the row's column i0 in the projection
 #pragma unroll 1
-      for (int j = j0; j <= j1 && !deferred; ++j) {
-        const float vv = vt[j];
-        const float y = (float)(j - j0) * A.dv;
-        const float* yr = yrow + (size_t)j * nu;
-        float R[6];
+      do {
+        if (k > k_hi) {
+          ++j;
+          vv = vt[j];
+          const float y = (float)(j - j0) * A.dv;
+          row += nu;
 #pragma unroll
-        for (int e = 0; e < 6; ++e) R[e] = fmaf(y, cB[e], cC[e]);
-        float lo = 0.f, hi = box_hi;
-#pragma unroll
-        for (int e = 0; e < 6; ++e) {
-          const float t = (sb[e] - R[e]) * rA[e];
-          hi = upper[e] ? fminf(hi, t) : hi;
-          lo = lower[e] ? fmaxf(lo, t) : lo;
+          for (int e = 0; e < 6; ++e) R[e] = fmaf(y, cB[e], cC[e]);
+          const float hi = fminf(fmaf(y, uB[0], uA[0]), fminf(fmaf(y, uB[1], uA[1]), fmaf(y, uB[2], uA[2])));
+          const float lo = fmaxf(fmaf(y, lB[0], lA[0]), fmaxf(fmaf(y, lB[1], lA[1]), fmaf(y, lB[2], lA[2])));
+          k = (int)ceilf(__builtin_amdgcn_fmed3f(lo, 0.f, box_hi));
+          k_hi = (int)floorf(__builtin_amdgcn_fmed3f(hi, -1.f, box_hi));
         }
-        // Slack for the rounding of t (relative) and of the comparison.
-        hi = fmaxf(hi + fmaf(fabsf(hi), 0x1p-22f, 0x1p-10f), -1.0f);
-        lo = fminf(lo - fmaf(fabsf(lo), 0x1p-22f, 0x1p-10f), box_hi + 1.0f);
-        const int ilo = i0 + max(0, (int)ceilf(lo)), ihi = i0 + min(i1 - i0, (int)floorf(hi));
-#pragma unroll 1
-        for (int i = ilo; i <= ihi; ++i) {
-          // Issued first so that their latency overlaps the classification.
-          const float yv = yr[i];
-          const float uu = ut[i];
-          const float kx = (float)(i - i0);
-          float E[6];
+        // A row without pixels leaves a turn without one.  No branch per lane
+        // from here on: a miss adds zero.
+        const unsigned long long in = __ballot(k <= k_hi);
+        const float kx = (float)k;
+        // Issued first so that their latency overlaps the classification.
+        const float yv = yrow[row + k];
+        const float uu = ut[i0 + k];
+        ++k;
+        float E[6];
 #pragma unroll
-          for (int e = 0; e < 6; ++e) E[e] = fmaf(kx, cA[e], R[e]);
-          float g[4];
-          face_max(E, g);
-          const float m = fminf(fminf(g[0], g[1]), fminf(g[2], g[3]));
-          if (m > bound) continue;
-          float h[4];
-          face_min(E, h);
-          const float M = fmaxf(fmaxf(h[0], h[1]), fmaxf(h[2], h[3]));
-          int fe = 3, fx = 3;
-          fe = g[2] == m ? 2 : fe;
-          fe = g[1] == m ? 1 : fe;
-          fe = g[0] == m ? 0 : fe;
-          fx = h[2] == M ? 2 : fx;
-          fx = h[1] == M ? 1 : fx;
-          fx = h[0] == M ? 0 : fx;
-          fx = (m < -bound && M > bound) ? fx : -1;
-          const float3 P = pixel_point(F.f, uu, vv);
-          const double dx = (double)P.x - F.Sx, dy = (double)P.y - F.Sy, dz = (double)P.z - F.Sz;
-          if (fx < 0) {
+        for (int e = 0; e < 6; ++e) E[e] = fmaf(kx, cA[e], R[e]);
+        float g[4], h[4];
+        face_max(E, g);
+        const float m = fminf(fminf(g[0], g[1]), fminf(g[2], g[3]));
+        face_min(E, h);
+        const float M = fmaxf(fmaxf(h[0], h[1]), fmaxf(h[2], h[3]));
+        int fe = 3, fx = 3;
+        fe = g[2] == m ? 2 : fe;
+        fe = g[1] == m ? 1 : fe;
+        fe = g[0] == m ? 0 : fe;
+        fx = h[2] == M ? 2 : fx;
+        fx = h[1] == M ? 1 : fx;
+        fx = h[0] == M ? 0 : fx;
+        const float3 P = pixel_point(ff, uu, vv);
+        const double dx = (double)P.x - fr[0], dy = (double)P.y - fr[1], dz = (double)P.z - fr[2];
+        unsigned long long hits = in & __ballot(m < -bound) & __ballot(M > bound);
+        const unsigned long long unsure = in & ~__ballot(m > bound) & ~hits;
+        if (__builtin_expect(unsure != 0, 0)) {
+          if (__builtin_amdgcn_inverse_ballot_w64(unsure)) {
             // Per-edge route: certain float signs, float64 3-D values for
             // the rest, the exact pass for what float64 cannot decide.
             int pos = 0, neg = 0;
@@ -413,13 +508,13 @@ __global__ __launch_bounds__(kShadowThreads, 4) void shadow_fast_kernel(ShadowAr
             }
             int unk = 0x3f & ~(pos | neg);
             if (unk) {
-              const float3 df = f3sub(P, F.S);
+              const float3 df = f3sub(P, S);
               const float dinf = fmaxf(fabsf(df.x), fmaxf(fabsf(df.y), fabsf(df.z)));
               while (unk) {
                 const int e = __ffs(unk) - 1;
                 unk &= unk - 1;
                 const int pe = (0x211000 >> (4 * e)) & 3, qe = (0x332321 >> (4 * e)) & 3;
-                const int s = edge_sign_fp64(F, dx, dy, dz, dinf, tet_vertex(tq, pe), tet_vertex(tq, qe), nullptr);
+                const int s = edge_sign_fp64(S, dx, dy, dz, dinf, tet_vertex(tq, pe), tet_vertex(tq, qe), nullptr);
                 st.fp64++;
                 if (s == 0) {
                   deferred = true;
@@ -428,28 +523,35 @@ __global__ __launch_bounds__(kShadowThreads, 4) void shadow_fast_kernel(ShadowAr
                 pos |= (s > 0) << e;
                 neg |= (s < 0) << e;
               }
-              if (deferred) break;
             }
             fe = entry_face(neg, pos);
-            if (fe < 0) continue;
             fx = entry_face(pos, neg);
-            if (fx < 0) continue;  // cannot happen for a valid tetrahedron
+            if (deferred) {  // through with this angle
+              j = j1;
+              k = k_hi + 1;
+            }
           }
-          st.hits++;
-          const double2 e0 = s_plane[fe][0][lane], e1 = s_plane[fe][1][lane];
-          const double2 x0 = s_plane[fx][0][lane], x1 = s_plane[fx][1][lane];
-          const double de = fma(dx, e0.x, fma(dy, e0.y, dz * e1.x));
-          const double dxx = fma(dx, x0.x, fma(dy, x0.y, dz * x1.x));
-          // t_x - t_e = (n_x d_e - n_e d_x) / (d_x d_e); the float64
-          // numerator keeps the cancellation harmless.
-          const double num = fma(x1.y, de, -(e1.y * dxx));
-          const float3 df = f3sub(P, F.S);
-          const float dn = __builtin_amdgcn_sqrtf(fmaf(df.x, df.x, fmaf(df.y, df.y, df.z * df.z)));
-          float L = (float)num * dn * __builtin_amdgcn_rcpf((float)(dxx * de));
-          L = fmaxf(L, 0.f);
-          acc = fma((double)L, (double)yv, acc);
+          // (An entry without an exit cannot happen for a valid tetrahedron.)
+          hits |= unsure & ~__ballot(deferred) & __ballot(fe >= 0) & __ballot(fx >= 0);
+          fe = max(fe, 0);
+          fx = max(fx, 0);
         }
-      }
+        const bool hit = __builtin_amdgcn_inverse_ballot_w64(hits);
+        st.hits += hit ? 1 : 0;
+        const double2 e0 = s_plane[fe][0][lane], e1 = s_plane[fe][1][lane];
+        const double2 x0 = s_plane[fx][0][lane], x1 = s_plane[fx][1][lane];
+        const double de = fma(dx, e0.x, fma(dy, e0.y, dz * e1.x));
+        const double dxx = fma(dx, x0.x, fma(dy, x0.y, dz * x1.x));
+        // t_x - t_e = (n_x d_e - n_e d_x) / (d_x d_e); the float64
+        // numerator keeps the cancellation harmless.
+        const double num = fma(x1.y, de, -(e1.y * dxx));
+        const float3 df = f3sub(P, S);
+        const float dn = __builtin_amdgcn_sqrtf(fmaf(df.x, df.x, fmaf(df.y, df.y, df.z * df.z)));
+        float L = (float)num * dn * __builtin_amdgcn_rcpf((float)(dxx * de));
+        L = fmaxf(L, 0.f);
+        L = hit ? L : 0.f;
+        acc = fma((double)L, (double)(hit ? yv : 0.f), acc);
+      } while (k <= k_hi || j < j1);
     }
     if (deferred) {
       int k = atomicAdd(A.dirty_count, 1);
@@ -539,7 +641,7 @@ __global__ __launch_bounds__(kShadowThreads) void shadow_exact_kernel(ShadowArgs
           const int pe = e < 3 ? 0 : (e < 5 ? 1 : 2);
           const int qe = e < 3 ? e + 1 : (e < 5 ? e - 1 : 3);
           double Ed;
-          int s = edge_sign_fp64(F, dx, dy, dz, dinf, v[pe], v[qe], &Ed);
+          int s = edge_sign_fp64(F.S, dx, dy, dz, dinf, v[pe], v[qe], &Ed);
           E[e] = (float)Ed;
           pos |= (s > 0) << e;
           neg |= (s < 0) << e;
@@ -602,8 +704,6 @@ __global__ void shadow_reduce_kernel(const double* partial, int chunks, int nt, 
   for (int k = 0; k < chunks; ++k) s += partial[(size_t)k * nt + t];
   xhat[t] = (float)s;
 }
-
-__global__ void zero_int_kernel(int* p) { *p = 0; }
 
 }  // namespace
 
@@ -681,16 +781,19 @@ tct_status backproject_shadow(const tct_mesh* m, const tct_geom* g, const float*
   int chunks = (int)std::max<int64_t>(1, std::min<int64_t>(a_count, (kShadowTargetWaves + waves - 1) / waves));
   A.chunk_len = (a_count + chunks - 1) / chunks;
   chunks = (a_count + A.chunk_len - 1) / A.chunk_len;
-  // Scratch: [counter][pad][deferred items: chunks * nt][float64 partials when chunked].
+  // Scratch: [counter][pad][deferred items: chunks * nt][frames][float64 partials when chunked].
   size_t items = (size_t)chunks * m->nt;
-  size_t off_part = ((16 + 4 * items) + 255) & ~(size_t)255;
+  const size_t off_frames = ((16 + 4 * items) + 255) & ~(size_t)255;
+  const size_t off_part = off_frames + (sizeof(double) * kFrameValues * (size_t)a_count + 255) / 256 * 256;
   size_t bytes = off_part + (chunks > 1 ? sizeof(double) * items : 0);
   void* scratch = nullptr;
   TCT_HIP(hipMallocAsync(&scratch, bytes, s));
   A.dirty_count = (int*)scratch;
   A.dirty = (int*)((char*)scratch + 16);
   A.partial = chunks > 1 ? (double*)((char*)scratch + off_part) : nullptr;
-  hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, s, A.dirty_count);
+  A.frames = (const double*)((char*)scratch + off_frames);
+  hipLaunchKernelGGL(shadow_prepare_kernel, dim3((unsigned)((a_count + 63) / 64)), dim3(64), 0, s, A,
+                     (double*)((char*)scratch + off_frames));
   const bool lds = g->cone.nu <= kShadowLdsTable && g->cone.nv <= kShadowLdsTable;
   dim3 grid((unsigned)blocks, (unsigned)chunks), block(kShadowThreads);
   if (lds)

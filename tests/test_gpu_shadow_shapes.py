@@ -24,6 +24,7 @@ SHAPES = {
     "small shadows, ties": ("plain", 12, 13, 11, 4),
     "one column": ("plain", 4, 1, 65, 6),
     "one row": ("jittered", 4, 65, 1, 20),
+    "more columns than the table in LDS holds": ("jittered", 3, 2300, 3, 3),
 }
 
 
