@@ -286,17 +286,27 @@ __device__ int find_entry(const MeshView& M, const Ray& r, St& st) {
 // Instead each wavefront sums its segments per tetrahedron in its own LDS
 // open-addressing table (key = tetrahedron) and adds one global atomic (two
 // or three for the exact sums) per distinct tetrahedron when it flushes the
-// table.  The rays advance in windows of a
-// fixed number of steps and the wavefront flushes its table after each
+// table.  The rays advance in windows of some steps and the wavefront flushes
+// its table after each
 // window, so the table only holds the tetrahedra of one window of its ray
 // bundle (an 8 x 8 bundle meets about 170 tetrahedra per 32 steps, 300 per
 // 64 steps on the benchmark mesh); a segment that finds no slot within
 // kLdsProbes probes goes straight to global memory.  Tables are private to a
 // wavefront, so a window ends without any block-wide barrier and each
-// wavefront runs at its own pace.  512 slots and windows of 40 steps are the
-// best of 384 / 28 .. 768 / 64 for the scatters (90 angles of the benchmark
-// 20.4 ms, against 20.8 and 20.9; coarser detectors within 3%), and keep four
-// wavefronts per SIMD.
+// wavefront runs at its own pace.
+//
+// 512 slots keep four wavefronts per SIMD (1024 keep three: 90 angles of the
+// benchmark 19.1 ms instead of 17.1; 768, with windows of 24 to 48, 17.4 to
+// 17.1).  A window costs its flush, a full table its probes: windows of 12,
+// 20, 24, 28, 32 and 40 steps take 19.3, 17.2, 17.0, 16.9, 17.0 and 17.1 ms,
+// and the exact sums, whose flush has two or three atomics a tetrahedron,
+// 24.5, 19.9, 19.1, 18.8, 18.6 and 18.5.  So they start with 28 and 36 steps.
+// Rays further apart have fewer tetrahedra in common and fill the table
+// sooner: a wavefront that has used more than kFull slots goes on with half the
+// window.  200 angles of 128 x 128 through the 64^3 mesh, two elements a pixel,
+// take 15.8 ms with 40 steps, 13.9 with 28 and 10.6 with 28 halved as needed.
+// (Growing windows for the opposite case gain nothing and cost small
+// launches 5%.)
 //
 // The tables sum in 64-bit fixed point: LDS integer atomics run several
 // times faster than float ones on this chip.  Each term t = L y_j |d| is
@@ -308,7 +318,7 @@ __device__ int find_entry(const MeshView& M, const Ray& r, St& st) {
 // of the terms that matter.  Terms below 2^51 in magnitude are converted to
 // integers with one float64 addition (round_to_i64).
 constexpr int kScatterSlots = 512;
-constexpr int kScatterWindow = 40;
+constexpr int kMinWindow = 12;
 constexpr int kLdsProbes = 8;
 constexpr int kGroupBits = 2;  // slots hold aligned groups of 4 tetrahedra (table_home)
 constexpr int kBlockWaves = 4;
@@ -801,7 +811,8 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
   int segments = 0;
   if constexpr (kTable) {
     const int lane = threadIdx.x & 63;
-    constexpr int kSlots = kScatterSlots, kWindow = kScatterWindow;
+    constexpr int kSlots = kScatterSlots;
+    constexpr int kStart = MODE == kModeBackExact ? 36 : 28, kFull = MODE == kModeBackExact ? 340 : 288;  // see kScatterSlots
     lds_i32* keys = (lds_i32*)tkeys + kSlots * wave_in_block();
     lds_i64* vals = (lds_i64*)tvals + kSlots * wave_in_block();
     for (int k = lane; k < kSlots; k += 64) {
@@ -856,12 +867,12 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
       o.lds_scale = ldexpf(1.0f, o.scale_exp);
     }
     o.weight *= o.lds_scale;  // a power of two: exact
-    // The wavefront's rays advance together in windows of kWindow
+    // The wavefront's rays advance together in windows of `window`
     // steps; after each window its table is added to xhat and cleared, so it
     // only ever holds the tetrahedra of one window of the ray bundle.  (All
     // live rays have taken the same number of steps, `taken` at a window's
     // start, where the step bound is checked.)
-    int taken = 0;
+    int taken = 0, window = kStart;
     for (;;) {
       // Each step claims the slot of the tetrahedron it enters (walk_step);
       // the flush has cleared the table, so the current ones claim again.
@@ -873,14 +884,18 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
         st.add_failed();
         w.packed = -1;
       }
-      segments += walk_steps<MODE>(M, r, q, w, o, st, kWindow);
-      taken += kWindow;
+      segments += walk_steps<MODE>(M, r, q, w, o, st, window);
+      taken += window;
       // LDS operations of one wavefront complete in order: the flush sees
       // every add of the window.
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      for (int k = lane; k < kSlots; k += 64) {
+      int used = 0;
+#pragma unroll 1
+      for (int b = 0; b < kSlots; b += 64) {  // (a scalar counter: the sum over wavefronts stays scalar)
+        const int k = b + lane;
         const int key = keys[k];
+        used += __popcll(__ballot(key >= 0));
         if (key >= 0) {
           const long long v = vals[k];
           if (v != 0) {
@@ -898,6 +913,7 @@ __device__ __forceinline__ void walk_block(const MeshView& M, const GeomView& G,
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
       if (__ballot(w.packed >= 0) == 0) break;
+      if (used > kFull) window = max(window / 2, kMinWindow);  // the next one would fill the table too
     }
     flush_stats(M, st, rays, segments);
   } else if constexpr (kEntryOnly) {

@@ -1,6 +1,6 @@
 """The scatters' wavefront tables where they are fullest and smallest: rays so
-far apart that a window of 40 steps meets more tetrahedra than the table has
-slots (probes wrap around and terms go straight to memory), meshes whose
+far apart that a window meets more tetrahedra than the table has slots (probes
+wrap around, terms go straight to memory, windows are halved), meshes whose
 tetrahedra do not fill the table's groups of four, and a detector of odd size.
 Every element against the oracle, within the bars of the other backprojection
 tests."""
