@@ -248,9 +248,7 @@ tct_status tct_geom_frame(const tct_geom* g, float* S, float* D, float* U, float
 void tct_geom_destroy(tct_geom* g) {
   if (!g) return;
   DeviceGuard dg(g->device);
-  if (g->d_frame) (void)hipFree(g->d_frame);
-  if (g->d_ut) (void)hipFree(g->d_ut);
-  if (g->d_vt) (void)hipFree(g->d_vt);
+  if (g->d_frame) (void)hipFree(g->d_frame);  // (d_ut and d_vt lie in it)
   delete g;
 }
 
