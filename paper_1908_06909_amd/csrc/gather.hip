@@ -17,11 +17,12 @@
 // the float scatter makes one.  The words lie word by word, not tetrahedron by
 // tetrahedron: the lanes of a flush hold neighbouring tetrahedra, whose equal
 // words then share a line (21.9 ms for 90 angles of the 512 x 512 benchmark,
-// 30.8 the other way, 20.2 for the float scatter).  Records written to memory,
+// 30.8 the other way, with the walk and windows of then; now 18.4, and 16.6 for
+// the float scatter).  Records written to memory,
 // counted, moved into a list per tetrahedron and added up from there, with a
 // wait of the host per chunk of angles, took 48.6 ms for these, and 90 for 48^3
 // 256 x 256 x 120 (walked twice, the buffer being sized from a guess), which
-// now takes 7.2.
+// now takes 6.6.
 #include "common.h"
 #include "kernels.h"
 

@@ -336,10 +336,11 @@ __device__ __forceinline__ int lds_cas(lds_i32* p, int tet) {
 // Consecutive tetrahedra are neighbours in the mesh (internal order), so the
 // lanes of a flush, a slot each, find the tetrahedra of one cell side by side
 // and their atomics leave as one request for a line of memory, which is what
-// the scatter waits for: 90 angles of the 512 x 512 benchmark take 23.6 ms
+// the scatter waits for: 90 angles of the 512 x 512 benchmark took 23.6 ms
 // with single tetrahedra hashed, 20.5 with groups of 4, 20.8 with 8 and 21.2
 // with 16 (fuller groups displace more keys), a 128 x 128 detector, whose rays
-// share few tetrahedra, 17.6, 15.9, 15.0 and 14.5.
+// share few tetrahedra, 17.6, 15.9, 15.0 and 14.5 (windows of 40 steps and the
+// walk of then; now 16.6 and 10.6 with groups of 4).
 // The hash is multiplicative (Fibonacci) in 24 bits: the low 24 bits of k A, A
 // the golden-ratio fraction of 2^24, are the fractional part of k times 0.618,
 // which spreads consecutive groups over the table; its top 20 bits are scaled
