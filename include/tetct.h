@@ -266,8 +266,9 @@ tct_status tct_forward(const tct_mesh* m, const tct_geom* g, const float* x, flo
  *         bitwise-identical results run to run.  GATHER allocates stream-ordered
  *         scratch (64 bytes per tetrahedron for up to 2^26 rays); SHADOW does
  *         not use `entry`, never synchronises, and allocates stream-ordered
- *         float64 partial sums only when the mesh has too few elements to fill
- *         the device (then angles are split into chunks summed in order). */
+ *         scratch (4 bytes per tetrahedron, 128 per angle) and, when the mesh has
+ *         too few elements to fill the device, float64 partial sums (then angles
+ *         are split into chunks summed in order). */
 tct_status tct_backproject(const tct_mesh* m, const tct_geom* g, const float* proj, float* xhat, int mode,
                            int accumulate, const int32_t* entry, tct_stream s);
 

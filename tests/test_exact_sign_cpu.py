@@ -1,8 +1,8 @@
 """The exact determinant signs behind the walk's filters, run on the CPU,
 against rational arithmetic.
 
-Columns whose scaled entries are integers below 2^41 are decided in 128-bit
-integers, all others by the floating-point expansion; both must give the
+Columns whose scaled entries are integers below 2^42 are decided in integers of
+30-bit digits, all others by the floating-point expansion; both must give the
 sign of the exact determinant, and the two must agree wherever both apply.
 The inputs sit where the integer route can go wrong: exact zeros and their
 nearest neighbours, entries as large as the route admits in all nine places
