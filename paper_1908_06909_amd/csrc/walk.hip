@@ -987,10 +987,15 @@ __global__ __launch_bounds__(256, 4) void pixel_walk_kernel(MeshView M, GeomView
 // face, then the wavefront walks the candidate faces one by one with a lane
 // per pixel of the face's box.  When faces and angles are too few to fill
 // the chip (coarse meshes, single projections), gridDim.z wavefronts share
-// the boxes of 64 faces, taking interleaved runs of 64 pixels across faces: a
-// box of one or two runs keeps one or two of them busy, all boxes together
-// keep all.  Each box shared by itself took 53 us at 8^3 64x64x16 and 63 at
-// 24^3 128x128x20; now 19 and 33.
+// the boxes of 64 faces, taking interleaved runs of 64 pixels, numbered across
+// faces: a box of one or two runs keeps one or two of them busy, all boxes
+// together keep all.  Each box shared by itself takes 73 us for an
+// unjittered 8^3 64x64x16 and 62 for 16^3 128x96x20; now 26 and 35.  Where a
+// wavefront's runs begin in each box is found for all 64 faces at once, before
+// the walk over them, whose instructions a face count where boxes are of a run
+// or two: counting on from face to face took 2.02 ms for the benchmark's 94.4M
+// rays and 131 us for a Delaunay mesh of 403,084 elements seen at 256x256x30;
+// now 1.85 and 111 (each box by itself 1.83 and 114).
 constexpr int kRasterWaves = 4;
 
 __device__ __forceinline__ void raster_box(const GeomView& G, const float* f, float3 a0, float3 a1, float3 a2,
@@ -1073,34 +1078,49 @@ __global__ __launch_bounds__(64 * kRasterWaves) void entry_raster_kernel(MeshVie
                &i0, &i1, &j0, &j1);
   }
   RegStats st(nullptr);
-  // Each face's box in runs of 64 pixels, the runs of all faces numbered
-  // through: this wavefront takes every gridDim.z-th of them.
-  const int w = i1 - i0 + 1;
-  const int64_t runs = i0 <= i1 && j0 <= j1 ? ((int64_t)w * (j1 - j0 + 1) + 63) / 64 : 0;
-  const int my_runs = (int)(runs < 0x7fffffff ? runs : 0x7fffffff);
-  unsigned long long todo = __ballot(my_runs > 0);
-  int64_t next = blockIdx.z;  // its next run, counted from the current face's first
+  // Each face's box in runs of 64 pixels, of which this wavefront takes every
+  // gridDim.z-th, from the lane's `first` on.  The runs of all faces are numbered
+  // through, so that `first` goes on where the face before has ended.  (The
+  // counts may wrap around: any start is right that every wavefront has for
+  // itself.)
+  const int z = (int)blockIdx.z, nz = (int)gridDim.z;
+  const int64_t mine = i0 <= i1 && j0 <= j1 ? (int64_t)(i1 - i0 + 1) * (j1 - j0 + 1) : 0;
+  int first = 0;
+  if (nz > 1) {
+    const unsigned runs = (unsigned)((mine + 63) / 64) % (unsigned)nz;
+    unsigned before = runs;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned x = __shfl_up(before, o, 64);
+      before += lane >= o ? x : 0u;
+    }
+    before = (before - runs) % (unsigned)nz;
+    first = z - (int)before + (z < (int)before ? nz : 0);
+  }
+  unsigned long long todo = __ballot((int64_t)first * 64 < mine);
   while (todo) {
     const int src = __ffsll((long long)todo) - 1;
     todo &= todo - 1;
-    const int n = __builtin_amdgcn_readlane(my_runs, src);
-    if (next < n) {
-      const int fb = __builtin_amdgcn_readlane(b, src), fi0 = __builtin_amdgcn_readlane(i0, src);
-      const int fj0 = __builtin_amdgcn_readlane(j0, src), fj1 = __builtin_amdgcn_readlane(j1, src);
-      const int fw = __builtin_amdgcn_readlane(w, src);
-      do {
-        const int64_t k = next * 64 + lane;
-        const int64_t row = k < 0x7fffffff ? (unsigned)k / (unsigned)fw : k / fw;
-        const int i = fi0 + (int)(k - row * fw);
-        const int64_t j = fj0 + row;
-        if (j <= fj1) {
-          const Ray r = cone_ray(G, M.extent, a, i, (int)j);
-          if (enters_face(M, r, fb, st)) entry[((int64_t)a * G.nv + j) * G.nu + i] = fb;
-        }
-        next += gridDim.z;
-      } while (next < n);
+    const int fb = __shfl(b, src, 64), fi0 = __shfl(i0, src, 64), fi1 = __shfl(i1, src, 64);
+    const int fj0 = __shfl(j0, src, 64), fj1 = __shfl(j1, src, 64);
+    const int w = fi1 - fi0 + 1;
+    const int64_t n = (int64_t)w * (fj1 - fj0 + 1);
+    const int at = lane + 64 * __shfl(first, src, 64);
+    if (n < 0x7fff0000) {  // 32-bit indices (k + 64 gridDim.z cannot overflow) unless the box is huge
+      for (int k = at; k < (int)n; k += 64 * nz) {
+        const int row = k / w;
+        const int i = fi0 + (k - row * w), j = fj0 + row;
+        const Ray r = cone_ray(G, M.extent, a, i, j);
+        if (enters_face(M, r, fb, st)) entry[((int64_t)a * G.nv + j) * G.nu + i] = fb;
+      }
+    } else {
+      for (int64_t k = at; k < n; k += 64 * nz) {
+        const int64_t row = k / w;
+        const int i = fi0 + (int)(k - row * w), j = fj0 + (int)row;
+        const Ray r = cone_ray(G, M.extent, a, i, j);
+        if (enters_face(M, r, fb, st)) entry[((int64_t)a * G.nv + j) * G.nu + i] = fb;
+      }
     }
-    next -= n;
   }
   flush_stats(M, st, 0);
 }
@@ -1568,10 +1588,13 @@ tct_status entry_raster(const tct_mesh* m, const tct_geom* g, int32_t* entry, hi
     MeshView M = m->view();
     GeomView G = g->view();
     const unsigned gx = (unsigned)((m->nb + 64 * kRasterWaves - 1) / (64 * kRasterWaves));
-    // Split each face's box over several wavefronts when fewer than about
-    // 32 per compute unit would run otherwise.
+    // Share the boxes of 64 faces among several wavefronts when fewer than
+    // 48 per compute unit would run otherwise, three times what it holds at
+    // once: with 16 and 32 the Delaunay mesh above takes 132 and 121 us
+    // instead of 111, one of sizes 1 : 1000 with rays through its smallest
+    // 108 and 98 instead of 91.
     const int64_t waves = (int64_t)gx * kRasterWaves * g->na;
-    const unsigned nz = (unsigned)std::max<int64_t>(1, std::min<int64_t>(64, (8192 + waves - 1) / waves));
+    const unsigned nz = (unsigned)std::max<int64_t>(1, std::min<int64_t>(64, (12288 + waves - 1) / waves));
     for (int a0 = 0; a0 < g->na; a0 += 65535) {
       const unsigned ny = (unsigned)std::min(65535, g->na - a0);
       hipLaunchKernelGGL(entry_raster_kernel, dim3(gx, ny, nz), dim3(64 * kRasterWaves), 0, s, M, G, a0, entry);
