@@ -281,6 +281,14 @@ tct_status mesh_build(const float* verts, int32_t nv, const int32_t* tets, int32
       m->lo[k] = std::min(m->lo[k], P(v)[k]);
       m->hi[k] = std::max(m->hi[k], P(v)[k]);
     }
+  // The longest edge as the walk's step measures it: the float32 difference that
+  // it forms (walk_filter.h, step_edges), so that no step's edge is longer.
+  for (int t = 0; t < nt; ++t)
+    for (int i = 1; i < 4; ++i)
+      for (int j = 0; j < i; ++j)
+        for (int k = 0; k < 3; ++k)
+          m->edge_max = std::max(m->edge_max,
+                                 std::fabs(P(Ts[4 * (size_t)t + i])[k] - P(Ts[4 * (size_t)t + j])[k]));
   // Internal order: Morton curve of the tetrahedron centroids.
   m->perm.resize(nt);
   std::iota(m->perm.begin(), m->perm.end(), 0);
@@ -476,8 +484,6 @@ tct_status mesh_build(const float* verts, int32_t nv, const int32_t* tets, int32
     float c[12];
     for (int k = 0; k < 4; ++k)
       for (int x = 0; x < 3; ++x) c[3 * k + x] = P(idx[k])[x];
-    for (int k = 0; k < 12; ++k)
-      for (int j = k + 3; j < 12; j += 3) m->edge_max = std::max(m->edge_max, std::fabs(c[k] - c[j]));
     for (int w = 0; w < 3; ++w) tetxyz[3 * (size_t)i + w] = make_float4(c[4 * w], c[4 * w + 1], c[4 * w + 2], c[4 * w + 3]);
   }
   tct_status st;
