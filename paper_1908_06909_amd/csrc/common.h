@@ -122,16 +122,14 @@ __host__ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t n) {
 #endif
 }
 
-// Local-index remap, tabulated for the walk.  The walk keeps the local indices of its
-// three entry-face slots and of v in 2-bit fields of one byte (slot j in bits
-// 2j, v in bits 6-7).  Leaving through the face opposite slot k into a
-// neighbour whose opposite vertex has local index `back`, every index p
-// becomes r + (r >= back) with r = p - (p > f), f = the index in slot k; slot
-// k then takes v's new index and v's field takes `back`.  The entry for
-// (byte, k, back) sits at (byte * 3 + k) * 4 + back; bytes that are not
+// Local-index remap: what the walk's table (below) is made from.  The local
+// indices of the three entry-face slots and of v stand in 2-bit fields of one
+// byte (slot j in bits 2j, v in bits 6-7).  Leaving through the face opposite
+// slot k into a neighbour whose opposite vertex has local index `back`, every
+// index p becomes r + (r >= back) with r = p - (p > f), f = the index in slot
+// k; slot k then takes v's new index and v's field takes `back`.  The entry for
+// (byte, k, back) has the number (byte * 3 + k) * 4 + back; bytes that are not
 // permutations map to values the walk never reads.
-constexpr int kLocRemapEntries = 256 * 3 * 4;
-
 constexpr unsigned loc_remap_entry(unsigned i) {
   const unsigned L = i / 12u, k = (i / 4u) % 3u, back = i % 4u;
   const unsigned f = (L >> (2u * k)) & 3u;
@@ -145,6 +143,28 @@ constexpr unsigned loc_remap_entry(unsigned i) {
   out = (out & ~(3u << (2u * k))) | (vnew << (2u * k));
   return (out & 0x3Fu) | (back << 6);
 }
+
+// The table that the walk reads, without v's field, which follows from the other
+// three: one byte at loc << 4 | k << 2 | back, loc the fields of slots 0, 1, 2.
+constexpr int kRemapRows = 64 * 4;
+struct alignas(4) LocRemap {
+  unsigned char v[kRemapRows * 4];
+};
+
+constexpr LocRemap make_loc_remap() {
+  LocRemap t{};
+  for (unsigned loc = 0; loc < 64; ++loc)
+    for (unsigned k = 0; k < 3; ++k)
+      for (unsigned back = 0; back < 4; ++back) {
+        const unsigned v = (6u - (loc & 3u) - (loc >> 2 & 3u) - (loc >> 4)) & 3u;
+        t.v[(loc * 4 + k) * 4 + back] = (unsigned char)(loc_remap_entry(((loc | v << 6) * 3 + k) * 4 + back) & 0x3Fu);
+      }
+  return t;
+}
+
+// Where the four bytes of (loc, k) begin; sh = 2k is the bit where slot k's
+// field begins in loc.
+__host__ __device__ constexpr unsigned loc_remap_row(unsigned loc, unsigned sh) { return (loc << 4) | (sh << 1); }
 
 void set_error(const std::string& msg);
 tct_status hip_fail(hipError_t e, const char* what);

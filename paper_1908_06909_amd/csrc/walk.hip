@@ -461,26 +461,8 @@ struct WalkState {
   bool far;
 };
 
-// Local-index remap as a table of loc_remap_entry (common.h) without v's field,
-// which follows from the other three: one byte at loc << 4 | k << 2 | back,
-// copied into each block's LDS.  A read per step, in place of about fifteen
-// vector instructions.
-constexpr int kRemapRows = 64 * 4;
-struct alignas(4) LocRemap {
-  unsigned char v[kRemapRows * 4];
-};
-
-constexpr LocRemap make_loc_remap() {
-  LocRemap t{};
-  for (unsigned loc = 0; loc < 64; ++loc)
-    for (unsigned k = 0; k < 3; ++k)
-      for (unsigned back = 0; back < 4; ++back) {
-        const unsigned v = (6u - (loc & 3u) - (loc >> 2 & 3u) - (loc >> 4)) & 3u;
-        t.v[(loc * 4 + k) * 4 + back] = (unsigned char)(loc_remap_entry(((loc | v << 6) * 3 + k) * 4 + back) & 0x3Fu);
-      }
-  return t;
-}
-
+// The local-index remap (make_loc_remap, common.h), copied into each block's
+// LDS.  A read per step, in place of about fifteen vector instructions.
 __constant__ LocRemap kLocRemap = make_loc_remap();
 
 __shared__ __align__(4) unsigned char s_loc_remap[kRemapRows * 4];
@@ -650,7 +632,7 @@ __device__ __forceinline__ void walk_step(const MeshView& M, const Ray& r, const
     }
   }
   w.s_in += (double)dt;  // float64: no rounding drift along the ray
-  unsigned R = (L << 4) | (sh << 1);  // the remap's row (loc, k)
+  unsigned R = loc_remap_row(L, sh);
   // What does not need the record is done while it is in flight.  (An empty
   // statement that takes these values, so the compiler computes them here
   // rather than sinking them behind the wait for the record.)

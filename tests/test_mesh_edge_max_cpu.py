@@ -21,8 +21,7 @@ CSRC = os.path.join(ROOT, "paper_1908_06909_amd", "csrc")
 BUILD = os.path.join(ROOT, "_build")
 
 
-@pytest.fixture(scope="module")
-def edge_max():
+def probe_lib():
     os.makedirs(BUILD, exist_ok=True)
     out, src = os.path.join(BUILD, "libmesh_probe.so"), os.path.join(HERE, "mesh_probe.cpp")
     if not os.path.exists(out) or os.path.getmtime(out) < max(os.path.getmtime(f) for f in
@@ -32,7 +31,12 @@ def edge_max():
                         CSRC, "-I", os.path.join(ROOT, "include"), src, "-o", out + ".tmp"],
                        check=True, capture_output=True)
         os.replace(out + ".tmp", out)
-    fn = C.CDLL(out).probe_edge_max
+    return C.CDLL(out)
+
+
+@pytest.fixture(scope="module")
+def edge_max():
+    fn = probe_lib().probe_edge_max
     fn.argtypes, fn.restype = [C.c_void_p], C.c_float
     return fn
 
