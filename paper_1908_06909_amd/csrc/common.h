@@ -91,10 +91,15 @@ enum Counter {
 
 // Walk statistics are added in one of kCounterRows rows of counters, 64 bytes
 // each, and summed when they are read.  Every wavefront ends with such an
-// add, and adds to one line are served one after the other, about 8 ns each
-// whatever the number of counters in it: with a single row the forward walk
-// of 94.4M rays (1.47M wavefronts) could not take less than 62 ms, nor one of
-// 5.9M rays through a mesh of 196,608 tetrahedra less than 3.5 (2.0 now).
+// add, one atomic instruction for all its counters, and adds to one line are
+// served one after the other, about 8 ns each whatever the number of counters
+// in it.  An instruction for each counter, four to eight a wavefront and all on
+// one row, was what the forward walks waited for: 62 ms for 94.4M rays (1.47M
+// wavefronts), 3.5 for 5.9M through 196,608 tetrahedra (2.0 now).  The single
+// instruction gives most of that (1.47M of them in a row take 12 ms, beside a
+// walk of 50), the rows the rest: 2.0M rays through a Delaunay mesh of 403,084
+// tetrahedra take 1.07 ms with one row and 1.04 with 256, 23.6M through the
+// benchmark's 12.79 and 12.75.
 constexpr int kCounterRows = 256;
 
 // The row of the calling workgroup (neighbouring workgroups take different

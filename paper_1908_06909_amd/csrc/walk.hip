@@ -26,8 +26,9 @@
 // well defined through vertices, edges and face planes (the failure cases of
 // Section II-C, Fig. 3) without the paper's escalating epsilon.  It is first
 // estimated in float32 as (q - p) . ((P - S) x (p - S)) with a certified
-// error bound; the rare uncertain cases go to a non-inlined float64 /
-// exact-expansion routine (exact.h).
+// error bound; the rare uncertain cases go through a float64 filter to exact
+// integers, inline beside the step, and where these do not apply to exact
+// expansions in a function of their own (exact.h).
 #include <mutex>
 #include <type_traits>
 
@@ -304,7 +305,15 @@ __device__ int find_entry(const MeshView& M, const Ray& r, St& st) {
 // Rays further apart have fewer tetrahedra in common and fill the table
 // sooner: a wavefront that has used more than kFull slots goes on with half the
 // window.  200 angles of 128 x 128 through the 64^3 mesh, two elements a pixel,
-// take 15.8 ms with 40 steps, 13.9 with 28 and 10.6 with 28 halved as needed.
+// take 15.8 ms with 40 steps, 13.9 with 28 and 10.6 with 28 halved as needed
+// (exact sums 29.8 with 36, 19.2 halved), 11.4 when they are halved down to 7
+// steps instead of kMinWindow, 11.7 down to 18.  kFull from 224 to 352 gives the
+// same there; at 224 a Delaunay mesh of 403,084 tetrahedra, whose tables are
+// hardly half full, loses (1.50 ms instead of 1.39, as with 352 or no halving;
+// exact sums 2.04 at 280, 1.91 at 340, 1.88 at 400).  The rule loses where windows
+// stay about the threshold: on a mesh whose sizes span 1 : 470, seen by 2.0M rays
+// through its small ones, 298 slots a window, no halving takes 2.6 ms and halving
+// 3.2 (exact sums 4.0 and 4.4).
 // (Growing windows for the opposite case gain nothing and cost small
 // launches 5%.)
 //
@@ -340,7 +349,13 @@ __device__ __forceinline__ int lds_cas(lds_i32* p, int tet) {
 // with single tetrahedra hashed, 20.5 with groups of 4, 20.8 with 8 and 21.2
 // with 16 (fuller groups displace more keys), a 128 x 128 detector, whose rays
 // share few tetrahedra, 17.6, 15.9, 15.0 and 14.5 (windows of 40 steps and the
-// walk of then; now 16.6 and 10.6 with groups of 4).
+// walk of then; now 16.6 and 10.6 with groups of 4).  A displaced key keeps its
+// place in the group, so the table is four tables of 128 slots.  They fill
+// evenly: in windows of 28 steps of 12 tiles of 64 rays, 42.4 to 43.2 slots of
+// each on the benchmark's mesh, 48.0 to 48.7 on a Delaunay mesh of 403,084
+// tetrahedra, 74.5 to 74.8 on one whose sizes span 1 : 470, and moving the keys
+// within their group by bits of the hash leaves the share of displaced ones as
+// it is (11, 13 and 22%).
 // The hash is multiplicative (Fibonacci) in 24 bits: the low 24 bits of k A, A
 // the golden-ratio fraction of 2^24, are the fractional part of k times 0.618,
 // which spreads consecutive groups over the table; its top 20 bits are scaled

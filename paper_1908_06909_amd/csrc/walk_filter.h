@@ -176,13 +176,19 @@ __host__ __device__ __forceinline__ void step_edges(const Ray& r, double s, floa
 // The same bound from the longest edge of the whole mesh (the largest |e|_inf
 // of any edge, as rounded in float32): all three signs are those of E0, E1 and
 // E2 when this holds.  It spares the step the magnitudes of its own edges; a
-// mesh with elements of very different sizes comes back to them more often.
+// mesh with elements of very different sizes comes back to them more often, one
+// lane for its whole wavefront.  Forward walks under the step's own bound and
+// under this one: 90 angles of the benchmark 13.2 and 12.75 ms, a Delaunay mesh
+// of uniform points 1.07 and 1.04, one whose sizes span 1 : 1000 from the centre
+// outwards 0.645 and 0.638, and where nearly every step is in elements of 1/470 of
+// the longest edge 1.500 and 1.514, the most that it was seen to lose.
 __host__ __device__ __forceinline__ bool step_signs_certain(const StepEdges& g, float edge_max) {
   return fminf(fabsf(g.E0), fminf(fabsf(g.E1), fabsf(g.E2))) > fmaf(edge_max, g.K, kFilterAbs);
 }
 
-// One bound from the step's longest edge: returns the exit slot (0..2; 3 when all three signs agree, a failed
-// walk), or -1 when some sign is uncertain under that bound.
+// One bound from the step's longest edge: returns the exit slot (0..2; 3 when
+// all three signs agree, a failed walk), or -1 when some sign is uncertain under
+// that bound.
 __host__ __device__ __forceinline__ int step_exit_common(const StepEdges& g) {
   if (fminf(fabsf(g.E0), fminf(fabsf(g.E1), fabsf(g.E2))) > fmaf(fmaxf(g.m0, fmaxf(g.m1, g.m2)), g.K, kFilterAbs)) {
     const unsigned n = (__builtin_bit_cast(unsigned, g.E0) >> 31) | ((__builtin_bit_cast(unsigned, g.E1) >> 31) << 1) |
