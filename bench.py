@@ -546,6 +546,8 @@ def main():
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
             "frac": ach / HBM_PEAK_GBS,
+            "note": "achieved and frac count algorithmic bytes, nearly all of which the on-chip caches serve, so "
+                    "frac may exceed 1; traffic counts what the memory served",
             "traffic": traffic,
             "traffic_bytes_per_launch": traffic_bytes,
             "bytes_per_segment": bps,
