@@ -181,7 +181,8 @@ __host__ __device__ __forceinline__ void step_edges(const Ray& r, double s, floa
 // under this one: 90 angles of the benchmark 13.2 and 12.75 ms, a Delaunay mesh
 // of uniform points 1.07 and 1.04, one whose sizes span 1 : 1000 from the centre
 // outwards 0.645 and 0.638, and where nearly every step is in elements of 1/470 of
-// the longest edge 1.500 and 1.514, the most that it was seen to lose.
+// the longest edge 1.500 and 1.514 (with the entry search in the kernel 1.475
+// and 1.499, the most that it was seen to lose).
 __host__ __device__ __forceinline__ bool step_signs_certain(const StepEdges& g, float edge_max) {
   return fminf(fabsf(g.E0), fminf(fabsf(g.E1), fabsf(g.E2))) > fmaf(edge_max, g.K, kFilterAbs);
 }
